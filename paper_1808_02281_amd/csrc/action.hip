@@ -2,109 +2,223 @@
 // deterministic reductions shared by the action, the fused force action and the
 // leapfrog Hamiltonian.
 //
-// Action kernel: one thread per site computes the 34 loop products of eq. (18_6_6_3_0)
-// at its site and accumulates w_X = sum (3 - Re tr P_n) per class X in double. The last
-// product of every loop is replaced by its trace (124 products + 34 traces per site).
+// Action kernel: w_X = sum over sites and class-X loops of (3 - Re tr P), in double, with
+// the 34 loops of a site (eq. 18_6_6_3_0) closed from halves that meet in a trace. No
+// unitarity is assumed, so the links are read in full. With the two ways around the
+// (nu, rho) square of a site, P = U_{y,nu} U_{y+nu,rho} and Q = U_{y,rho} U_{y+rho,nu}:
+//   plaquette   tr(P Q^+);
+//   rectangles  tr((U_{y,nu} P_{y+nu}) (Q_y U_{y+nu+rho,nu})^+) and the same with nu and
+//               rho exchanged;
+//   cube loops  carry one side of the square along mu: (mu, nu, rho, -mu, -nu, -rho) is
+//               tr((U_{y,mu} P_{y+mu}) (Q_y U_{y+nu+rho,mu})^+), exchanging P and Q gives the
+//               loop with nu and rho both reversed, and the two loops with one of them
+//               reversed have the same form with the square's other two sides
+//               E = U_{y+rho,nu} U_{y+nu,rho}^+ and F = U_{y,rho}^+ U_{y,nu}.
+// Every loop is summed once over the lattice (its base site differs from the paper's by a
+// translation). Four (square, mu) pairs cover the four axis triples.
+//
+// A workgroup is 64 sites, its four waves share the loops: wave k takes the cube loops of
+// one (square, mu) pair and one or two squares' plaquette and rectangles. With one thread
+// per site multiplying out all 34 loops, what bounded the kernel was link data from beyond
+// the L2 (16 GB for 0.4 GB of links at 24^3 x 48 in FP64, 7.1 TB/s). 64 sites per workgroup
+// instead of 256 keep the links of the sites in flight on an XCD within its 4 MiB of L2
+// (1.5 GB fetched), in the t-fastest slab order of the force passes, and small lattices
+// get four times the waves with a quarter of the serial work each. The squares' axes are
+// wave-uniform values rather than template arguments, so the four waves share one code.
+// Measured, before -> now: FP64 24^3 x 48 2.25 -> 0.61 ms, FP32 32^3 x 64 3.37 -> 1.08 ms,
+// FP64 4^4 107 -> 17 us. The bound now is the vector load path (TD busy 0.94 in FP64, VALU
+// 0.44).
 #include "kernels.hpp"
-#include "path_table.hpp"
 
 namespace sym {
 namespace {
 
-struct LinkRef {
-  int off[4];
-  int ax;
-  bool dag;
+// Lexicographic index steps of one and two links forwards along an axis.
+struct Step {
+  int one, two;
 };
-
-struct LoopRefs {
-  int n;
-  int cls;
-  LinkRef r[6];
-};
-
-constexpr LoopRefs loop_refs(int l) {
-  LoopRefs out{};
-  const table::LoopDef& d = table::kLoop[l];
-  int p[4] = {0, 0, 0, 0};
-  out.n = d.len;
-  out.cls = d.cls;
-  for (int j = 0; j < d.len; ++j) {
-    const int a = (d.dir[j] > 0 ? d.dir[j] : -d.dir[j]) - 1;
-    if (d.dir[j] > 0) {
-      out.r[j] = LinkRef{{p[0], p[1], p[2], p[3]}, a, false};
-      p[a] += 1;
-    } else {
-      p[a] -= 1;
-      out.r[j] = LinkRef{{p[0], p[1], p[2], p[3]}, a, true};
-    }
-  }
-  return out;
-}
 
 template <typename T>
-struct SiteCtx {
+struct LoopSite {
   const T* U;
   int Vh;
   int p;
-  Nbr nb;
+  int lex;
 
-  template <int D0, int D1, int D2, int D3, int AX>
-  __device__ __forceinline__ su3<T> link() const {
-    constexpr int dp = offset_parity<D0, D1, D2, D3>();
-    return load_link(block_ptr(U, AX, p ^ dp, Vh), Vh, nbr_cb<D0, D1, D2, D3>(nb));
+  // U_{y+d, a} for the site y + d at lexicographic step `off` and parity flip k
+  __device__ __forceinline__ su3<T> link(int a, int k, int off) const {
+    return load_link(block_ptr(U, a, p ^ k, Vh), Vh, (lex + off) >> 1);
   }
 };
 
-#define SYM_LINK(ctx, R) (ctx).template link<(R).off[0], (R).off[1], (R).off[2], (R).off[3], (R).ax>()
-
-template <typename T, int LP>
-__device__ __forceinline__ void add_loop(const SiteCtx<T>& ctx, double w[3]) {
-  constexpr LoopRefs R = loop_refs(LP);
-  constexpr LinkRef a = R.r[0], b = R.r[1], c = R.r[2], d = R.r[3];
-  su3<T> m = mul<a.dag, b.dag>(SYM_LINK(ctx, a), SYM_LINK(ctx, b));
-  m = mul<false, c.dag>(m, SYM_LINK(ctx, c));
-  double rt;
-  if constexpr (R.n == 4) {
-    rt = re_tr_mul<d.dag>(m, SYM_LINK(ctx, d));
-  } else {
-    constexpr LinkRef e = R.r[4], f = R.r[5];
-    m = mul<false, d.dag>(m, SYM_LINK(ctx, d));
-    m = mul<false, e.dag>(m, SYM_LINK(ctx, e));
-    rt = re_tr_mul<f.dag>(m, SYM_LINK(ctx, f));
-  }
-  w[R.cls] += 3.0 - rt;
+// Fence between groups of loops: links that several groups read are loaded again (they hit
+// L1) rather than kept in registers, no load moves ahead of its group, and the group's sum
+// is finished where it stands (the compiler otherwise sinks the products to the use of w
+// and keeps every link alive until there).
+template <typename T>
+__device__ __forceinline__ LoopSite<T> next_group(const LoopSite<T>& s, double& w) {
+  LoopSite<T> r = s;
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" : "+s"(r.U), "+v"(w));
+  return r;
 }
 
-template <typename T, int LP>
-__device__ __forceinline__ void add_loops(const SiteCtx<T>& ctx, double w[3]) {
-  if constexpr (LP < table::kLoops) {
-    // Reload links per loop (they hit in cache) rather than keep shared ones live.
-    SiteCtx<T> local = ctx;
-    asm volatile("" : "+s"(local.U));
-    add_loop<T, LP>(local, w);
+__device__ __forceinline__ Step step_along(const Geom& g, const int x[4], int a) {
+  const int xa = a == 0 ? x[0] : a == 1 ? x[1] : a == 2 ? x[2] : x[3];
+  const int La = a == 0 ? g.L[0] : a == 1 ? g.L[1] : a == 2 ? g.L[2] : g.L[3];
+  const int stride = a == 0 ? 1 : a == 1 ? g.L[0] : a == 2 ? g.L[0] * g.L[1] : g.L[0] * g.L[1] * g.L[2];
+  Step s;
+  s.one = (xa + 1 < La ? 1 : 1 - La) * stride;
+  s.two = (xa + 2 < La ? 2 : 2 - La) * stride;
+  return s;
+}
+
+// Plaquette and both rectangles of the (nu, rho) square: 8 products, 3 traces.
+template <typename T>
+__device__ __forceinline__ void square_loops(const LoopSite<T>& s0, int nu, int rho, Step dn, Step dr, double w[3]) {
+  const LoopSite<T> s1 = next_group(s0, w[1]);
+  const su3<T> un = s1.link(nu, 0, 0), ur = s1.link(rho, 0, 0);
+  const su3<T> P = mul<false, false>(un, s1.link(rho, 1, dn.one));
+  const su3<T> Q = mul<false, false>(ur, s1.link(nu, 1, dr.one));
+  w[0] += 3.0 - re_tr_mul<true>(P, Q);
+  {  // long side along nu
+    const LoopSite<T> s = next_group(s1, w[0]);
+    const su3<T> a = mul<false, false>(un, mul<false, false>(s.link(nu, 1, dn.one), s.link(rho, 0, dn.two)));
+    const su3<T> b = mul<false, false>(Q, s.link(nu, 0, dn.one + dr.one));
+    w[1] += 3.0 - re_tr_mul<true>(a, b);
+  }
+  {  // long side along rho
+    const LoopSite<T> s = next_group(s1, w[1]);
+    const su3<T> a = mul<false, false>(ur, mul<false, false>(s.link(rho, 1, dr.one), s.link(nu, 0, dr.two)));
+    const su3<T> b = mul<false, false>(P, s.link(rho, 0, dn.one + dr.one));
+    w[1] += 3.0 - re_tr_mul<true>(a, b);
+  }
+  (void)next_group(s1, w[1]);
+}
+
+// The four cube loops of the (nu, rho) square carried along mu: 16 products, 4 traces. Two
+// orders of the same products. cube_loops_ring (FP32) finishes the square's four sides at
+// y first and then walks the square at y+mu corner by corner, each of its links serving
+// the two sides it lies on: 14 link loads. It holds six matrices and more, which in FP64
+// is 298 registers (one wave per SIMD) or spills; cube_loops_diag (FP64) takes the square's
+// two diagonals in turn, with 20 link loads, at two waves per SIMD. FP32, 32^3 x 64:
+// ring 1.08 ms, diag 1.21 ms; FP64, 24^3 x 48: ring 0.70 ms (one wave) or 0.80 ms (two
+// waves, 54 spilled registers), diag 0.61 ms.
+template <typename T>
+__device__ __forceinline__ void cube_loops_ring(const LoopSite<T>& s0, int nu, int rho, int mu, Step dn, Step dr, Step dm,
+                                                double w[3]) {
+  const LoopSite<T> s = next_group(s0, w[2]);
+  su3<T> P, Q, E, F;
+  {
+    const su3<T> a = s.link(nu, 0, 0), b = s.link(rho, 1, dn.one);
+    const su3<T> c = s.link(rho, 0, 0), d = s.link(nu, 1, dr.one);
+    const su3<T> um = s.link(mu, 0, dn.one + dr.one);
+    P = mul<false, false>(mul<false, false>(a, b), um);
+    Q = mul<false, false>(mul<false, false>(c, d), um);
+    const su3<T> un = s.link(mu, 1, dn.one);
+    E = mul<false, false>(mul<false, true>(d, b), un);
+    F = mul<false, false>(mul<true, false>(c, a), un);
+  }
+  const LoopSite<T> t = next_group(s, w[2]);
+  const su3<T> b1 = t.link(rho, 0, dn.one + dm.one);
+  {
+    const su3<T> u0 = t.link(mu, 0, 0);
+    const su3<T> P1 = mul<false, false>(t.link(nu, 1, dm.one), b1);
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u0, P1), Q);
+  }
+  LoopSite<T> v = next_group(t, w[2]);
+  const su3<T> d1 = v.link(nu, 0, dr.one + dm.one);
+  {
+    const su3<T> u1 = v.link(mu, 1, dr.one);
+    const su3<T> E1 = mul<false, true>(d1, b1);
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u1, E1), F);
+  }
+  v = next_group(v, w[2]);
+  const su3<T> c1 = v.link(rho, 1, dm.one);
+  {
+    const su3<T> u0 = v.link(mu, 0, 0);
+    const su3<T> Q1 = mul<false, false>(c1, d1);
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u0, Q1), P);
+  }
+  v = next_group(v, w[2]);
+  {
+    const su3<T> u1 = v.link(mu, 1, dr.one);
+    const su3<T> F1 = mul<true, false>(c1, v.link(nu, 1, dm.one));
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u1, F1), E);
+  }
+  (void)next_group(s0, w[2]);
+}
+
+template <typename T>
+__device__ __forceinline__ void cube_loops_diag(const LoopSite<T>& s0, int nu, int rho, int mu, Step dn, Step dr, Step dm,
+                                                double w[3]) {
+  {
+    const LoopSite<T> s = next_group(s0, w[2]);
+    const su3<T> um = s.link(mu, 0, dn.one + dr.one);
+    const su3<T> P = mul<false, false>(mul<false, false>(s.link(nu, 0, 0), s.link(rho, 1, dn.one)), um);
+    const su3<T> Q = mul<false, false>(mul<false, false>(s.link(rho, 0, 0), s.link(nu, 1, dr.one)), um);
     __builtin_amdgcn_sched_barrier(0);
-    add_loops<T, LP + 1>(ctx, w);
+    const su3<T> u0 = s.link(mu, 0, 0);
+    const su3<T> P1 = mul<false, false>(s.link(nu, 1, dm.one), s.link(rho, 0, dn.one + dm.one));
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u0, P1), Q);
+    __builtin_amdgcn_sched_barrier(0);
+    const su3<T> Q1 = mul<false, false>(s.link(rho, 1, dm.one), s.link(nu, 0, dr.one + dm.one));
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u0, Q1), P);
   }
+  {
+    const LoopSite<T> s = next_group(s0, w[2]);
+    const su3<T> um = s.link(mu, 1, dn.one);
+    const su3<T> E = mul<false, false>(mul<false, true>(s.link(nu, 1, dr.one), s.link(rho, 1, dn.one)), um);
+    const su3<T> F = mul<false, false>(mul<true, false>(s.link(rho, 0, 0), s.link(nu, 0, 0)), um);
+    __builtin_amdgcn_sched_barrier(0);
+    const su3<T> u1 = s.link(mu, 1, dr.one);
+    const su3<T> E1 = mul<false, true>(s.link(nu, 0, dr.one + dm.one), s.link(rho, 0, dn.one + dm.one));
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u1, E1), F);
+    __builtin_amdgcn_sched_barrier(0);
+    const su3<T> F1 = mul<true, false>(s.link(rho, 1, dm.one), s.link(nu, 1, dm.one));
+    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u1, F1), E);
+  }
+  (void)next_group(s0, w[2]);
 }
+
+template <typename T>
+__device__ __forceinline__ void cube_loops(const LoopSite<T>& s, int nu, int rho, int mu, Step dn, Step dr, Step dm,
+                                           double w[3]) {
+  if constexpr (sizeof(T) == 4)
+    cube_loops_ring(s, nu, rho, mu, dn, dr, dm, w);
+  else
+    cube_loops_diag(s, nu, rho, mu, dn, dr, dm, w);
+}
+
+constexpr int kActionSites = 64;  // sites per workgroup, one per lane of each of its waves
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void action_kernel(Geom g, const T* __restrict__ U, double* __restrict__ partials,
                                                         int ntiles) {
-  const int tile = xcd_tile(blockIdx.x, ntiles);
-  const int site = tile * kBlock + threadIdx.x;  // both parities: [0, Vh) even, [Vh, 2Vh) odd
+  const SiteTile st = site_tile(g, blockIdx.x, ntiles, kBlock / kActionSites);
+  const int cb = st.chunk * kActionSites + (threadIdx.x & 63);
   double w[3] = {0.0, 0.0, 0.0};
-  if (site < 2 * g.Vh) {
-    const int p = site >= g.Vh ? 1 : 0;
-    const int cb = site - p * g.Vh;
+  if (cb < g.Vh) {
     int x[4];
-    cb_coords(g, p, cb, x);
-    SiteCtx<T> ctx;
-    ctx.U = U;
-    ctx.Vh = g.Vh;
-    ctx.p = p;
-    make_nbr(g, x, ctx.nb);
-    add_loops<T, 0>(ctx, w);
+    cb_coords(g, st.p, cb, x);
+    LoopSite<T> s;
+    s.U = U;
+    s.Vh = g.Vh;
+    s.p = st.p;
+    s.lex = 2 * cb + (x[0] & 1);
+    // the waves' shares rotate with the workgroup, so that the two longer ones do not
+    // always land on the same SIMDs
+    const int k = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + (int)blockIdx.x) & 3;
+    // cube loops: squares 01, 01, 02, 12 carried along 2, 3, 3, 3
+    const int nu = k == 3 ? 1 : 0, rho = k < 2 ? 1 : 2, mu = k == 0 ? 2 : 3;
+    cube_loops(s, nu, rho, mu, step_along(g, x, nu), step_along(g, x, rho), step_along(g, x, mu), w);
+    // plaquettes and rectangles: squares 01, 23 | 02, 13 | 03 | 12
+    const int n1 = k == 3 ? 1 : 0, r1 = k == 0 ? 1 : k == 2 ? 3 : 2;
+    square_loops(s, n1, r1, step_along(g, x, n1), step_along(g, x, r1), w);
+    if (k < 2) {
+      const int n2 = k == 0 ? 2 : 1;
+      square_loops(s, n2, 3, step_along(g, x, n2), step_along(g, x, 3), w);
+    }
   }
   block_sum_store<3>(w, partials + 3 * (size_t)blockIdx.x);
 }
@@ -175,10 +289,7 @@ __global__ __launch_bounds__(64) void finish_stage2(const double* __restrict__ s
 
 }  // namespace
 
-int action_tiles(const Geom& g) {
-  const int n = (2 * g.Vh + kBlock - 1) / kBlock;
-  return (n + 7) & ~7;
-}
+int action_tiles(const Geom& g) { return site_tiles(g, kActionSites); }
 
 template <typename T>
 hipError_t launch_action(const Geom& g, const T* U, double* partials, hipStream_t s) {

@@ -92,25 +92,6 @@ def render():
             lines.append("    {%d, %d, {%s}},  // %s" % (cls, len(path), ", ".join("%2d" % v for v in dirs),
                                                          CLASS_NAMES[cls]))
         lines.append("  },")
-    lines += [
-        "};",
-        "",
-        "// The 34 loops per site (eq. 18_3_27_30), grouped by class, as direction sequences",
-        "// from the base site n back to n.",
-        "constexpr int kLoops = 34;",
-        "constexpr int kLoopClassBegin[4] = {0, 6, 18, 34};",
-        "",
-        "struct LoopDef {",
-        "  int cls;",
-        "  int len;",
-        "  int dir[6];",
-        "};",
-        "",
-        "constexpr LoopDef kLoop[34] = {",
-    ]
-    for cls, d in loops():
-        dirs = list(d) + [0] * (6 - len(d))
-        lines.append("  {%d, %d, {%s}},  // %s" % (cls, len(d), ", ".join("%2d" % v for v in dirs), CLASS_NAMES[cls]))
     lines += ["};", "", "}  // namespace table", "}  // namespace sym", ""]
     return "\n".join(lines)
 

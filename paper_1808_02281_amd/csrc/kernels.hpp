@@ -24,9 +24,9 @@ enum class ForceOut { Store = 0, Kick = 1, Grad = 2 };
 // Number of workgroups of a per-link launch (a multiple of 8: 4 directions x 2 parities)
 // with `links` links (threads) per workgroup.
 inline int link_tiles(const Geom& g, int links = kBlock) { return ((g.Vh + links - 1) / links) * 8; }
-// Number of workgroups of a per-site launch (2 parities per chunk, rounded up to a
-// multiple of 8 for the XCD-contiguous order).
-inline int site_tiles(const Geom& g) { return (((g.Vh + kBlock - 1) / kBlock) * 2 + 7) & ~7; }
+// Number of workgroups of a per-site launch of `sites` sites per workgroup (2 parities per
+// chunk, rounded up to a multiple of 8 for the XCD-contiguous order).
+inline int site_tiles(const Geom& g, int sites = kBlock) { return (((g.Vh + sites - 1) / sites) * 2 + 7) & ~7; }
 
 // Each per-link force launch writes 3 doubles per workgroup: sum of Re tr(U t_X).
 // The action kernel writes 3 per workgroup too (W_X partials).

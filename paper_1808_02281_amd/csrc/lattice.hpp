@@ -230,20 +230,21 @@ __device__ __forceinline__ LinkTile link_tile(const Geom& g, int linear, int nti
 // Per-site kernels (one thread per site of one parity): workgroup -> (parity,
 // 256-site chunk), the two parities of a chunk adjacent, with the same XCD slabs and
 // t-fastest walk as link_tile. ntiles is a multiple of 8; tiles past the lattice give
-// chunks whose sites lie beyond V/2 (the kernels skip them).
+// chunks whose sites lie beyond V/2 (the kernels skip them). split as for link_tile: chunks
+// of 256, 128 or 64 sites.
 struct SiteTile {
   int p, chunk;
 };
 
-__device__ __forceinline__ SiteTile site_tile(const Geom& g, int linear, int ntiles) {
+__device__ __forceinline__ SiteTile site_tile(const Geom& g, int linear, int ntiles, int split = 1) {
   const int tile = xcd_tile(linear, ntiles);
   SiteTile r;
   r.p = tile & 1;
   int chunk = tile >> 1;
   if (g.tslab > 0) {
-    const int per = ntiles >> 4;  // chunks per XCD = tslab * cps
+    const int per = ntiles >> 4;  // chunks per XCD = tslab * cps * split
     const int xcd = chunk / per, j = chunk - xcd * per;
-    chunk = (xcd * g.tslab + j % g.tslab) * g.cps + j / g.tslab;
+    chunk = (xcd * g.tslab + j % g.tslab) * (g.cps * split) + j / g.tslab;
   }
   r.chunk = chunk;
   return r;
