@@ -10,7 +10,8 @@
 //
 // Hopping (eqs. 18_1_29_20_1..3): with B' = sum_a ((1 - g_rho) X_{k+rho})_a (x) Y_{k,a}^+
 // and C' = sum_a X_{k,a} (x) ((1 + g_rho) Y_{k+rho})_a^+ (colour outer products summed
-// over spin a), B = U B' and C = C' U^+, and M_hop = -2 kappa (B - C).
+// over spin a), B = U B' and C = C' U^+, and M_hop = -2 kappa (B - C). Both spin sums need
+// only two terms, with both spinors projected (see outer).
 //
 // Clover: Y_n^+ G P X_n = tr(P S_n) for a colour matrix P with
 // S_n = sum_a (G X_n)_a (x) Y_{n,a}^+, so the clover part of Psi is
@@ -22,8 +23,10 @@
 //   M_clov = -(c_sw kappa / 8) U sum_{nu, s} sigma (abd K_c0 + K_c1 abd + a K_c2 bd + ab K_c3 d),
 // with a = U_{k+rho,nu_s}, b = U_{k+rho+nu_s,-rho}, d = U_{k+nu_s,-nu_s}, and
 // sigma = +-1 as the plaquette's sense rho -> nu_s agrees with the leaf sense min -> max.
-// The last two terms share their outer factors, a (K_c2 b + b K_c3) d: 8 products per
-// plaquette, 50 per link with U B' and C' U^+.
+// The last two terms share their outer factors, a (K_c2 b + b K_c3) d, and the first two have
+// the same K for both signs s of nu, so they act on the sum over s: 14 products per (rho, nu)
+// plane, 44 per link with U B' and C' U^+ (against 50 with each plaquette by itself: the
+// FP32 pass issues a VALU instruction on every cycle, so it pays by the instruction).
 //
 // Spinor layout: field[p][3*spin + colour][V/2] complex (parity p, checkerboard cb).
 // Clover insertions, pair = (0,1),(0,2),(0,3),(1,2),(1,3),(2,3): K is anti-Hermitian,
@@ -87,20 +90,6 @@ __device__ __forceinline__ spinor<T> gamma_apply(int mu, const spinor<T>& x) {
   return r;
 }
 
-// (1 + sgn gamma_mu) x
-template <typename T>
-__device__ __forceinline__ spinor<T> project(int mu, int sgn, const spinor<T>& x) {
-  const spinor<T> g = gamma_apply(mu, x);
-  spinor<T> r;
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      r.s[a][c] = sgn > 0 ? cx<T>{x.s[a][c].re + g.s[a][c].re, x.s[a][c].im + g.s[a][c].im}
-                          : cx<T>{x.s[a][c].re - g.s[a][c].re, x.s[a][c].im - g.s[a][c].im};
-  return r;
-}
-
 // sum over spin of the colour outer product: out_{ba} = sum_alpha p_{alpha b} conj(q_{alpha a})
 template <typename T>
 __device__ __forceinline__ su3<T> outer(const spinor<T>& p, const spinor<T>& q) {
@@ -140,6 +129,70 @@ __device__ __forceinline__ spinor<T> load_spinor(const T* F, int p, int Vh, int 
       s.s[e / 3][e % 3] = __builtin_bit_cast(cx<T>, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
   }
   return s;
+}
+
+// Spin components 0 and 1 of (1 + sgn gamma_rho) x at a site. They carry the whole
+// projection: component a is paired with b(a) by the one non-zero of row a of gamma_rho,
+// (1 + sgn gamma_rho) x is x_a + sgn phase_a x_{b(a)} there, and its components 2 and 3 are
+// phases times these two. rho is wave-uniform.
+template <typename T>
+struct half_spinor {
+  cx<T> s[2][3];
+};
+
+template <typename T>
+__device__ __forceinline__ half_spinor<T> load_projected(const T* F, int p, int Vh, int cb, int rho, T sgn) {
+  const cx<T>* blk = reinterpret_cast<const cx<T>*>(F) + (size_t)p * 12 * (size_t)Vh;
+  const unsigned bytes = 12u * (unsigned)Vh * (unsigned)sizeof(cx<T>);
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<cx<T>*>(blk), (short)0, (int)bytes,
+                                                                     kBufferWord3);
+  const int voff = cb * (int)sizeof(cx<T>);
+  const bool imag = rho == 0 || rho == 2;
+  half_spinor<T> h;
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const int b = rho < 2 ? 3 - a : 2 + a;
+    const T sg = (rho == 1 && a == 0) || (rho == 2 && a == 1) ? -sgn : sgn;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      cx<T> v[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const int soff = (int)((unsigned)(3 * (k ? b : a) + c) * (unsigned)Vh * (unsigned)sizeof(cx<T>));
+        if constexpr (sizeof(T) == 4)
+          v[k] = __builtin_bit_cast(cx<T>, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
+        else
+          v[k] = __builtin_bit_cast(cx<T>, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+      }
+      const T re = imag ? -v[1].im : v[1].re, im = imag ? v[1].re : v[1].im;
+      h.s[a][c] = cx<T>{fma(sg, re, v[0].re), fma(sg, im, v[0].im)};
+    }
+  }
+  return h;
+}
+
+// Colour outer product of two spinors projected with the same (1 +- gamma_rho) = 2 P:
+// sum over all four spins of (2P x)_b conj(y_a) = sum over two of (2P x)_b conj((2P y)_a),
+// since P is a Hermitian projector and the lower components repeat the upper ones.
+template <typename T>
+__device__ __forceinline__ su3<T> outer(const half_spinor<T>& p, const half_spinor<T>& q) {
+  su3<T> r;
+#pragma unroll
+  for (int b = 0; b < 3; ++b)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      T re = T(0), im = T(0);
+#pragma unroll
+      for (int al = 0; al < 2; ++al) {
+        const cx<T> x = p.s[al][b], y = q.s[al][a];
+        re = fma(x.re, y.re, re);
+        re = fma(x.im, y.im, re);
+        im = fma(x.im, y.re, im);
+        im = fma(-x.re, y.im, im);
+      }
+      r.e[3 * b + a] = cx<T>{re, im};
+    }
+  return r;
 }
 
 constexpr int pair_index(int lo, int hi) { return lo == 0 ? hi - 1 : (lo == 1 ? hi + 1 : 5); }
@@ -272,41 +325,93 @@ __device__ __forceinline__ su3<T> dagger(const su3<T>& a) {
   return r;
 }
 
-// acc += sigma (abd K0 + K1 abd + a K2 bd + ab K3 d) for the plaquette k, k+rho, k+rho+nu_s, k+nu_s
-// with nu = ax[J], s = S
+// C -= A B
+template <typename T>
+__device__ __forceinline__ void mac_neg(su3<T>& c, const su3<T>& a, const su3<T>& b) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      T re = c.e[3 * i + j].re, im = c.e[3 * i + j].im;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const cx<T> x = a.e[3 * i + k], y = b.e[3 * k + j];
+        re = fma(-x.re, y.re, re);
+        im = fma(-x.re, y.im, im);
+        re = fma(x.im, y.im, re);
+        im = fma(-x.im, y.re, im);
+      }
+      c.e[3 * i + j] = cx<T>{re, im};
+    }
+}
+
+// The plaquette k, k+rho, k+rho+nu_s, k+nu_s with nu = ax[J], s = S: abd into w and
+// a (K2 b + b K3) d into t, both set for S > 0 and subtracted for S < 0.
 template <int J, int S, typename T>
-__device__ __forceinline__ void clover_plaquette(su3<T>& acc, const WCtx<T>& c0) {
+__device__ __forceinline__ void clover_plaquette(su3<T>& t, su3<T>& w, const WCtx<T>& c0) {
   WCtx<T> c = c0;
   asm volatile("" : "+s"(c.U), "+s"(c.K));
   constexpr int e1 = J == 1 ? 1 : 0, e2 = J == 2 ? 1 : 0, e3 = J == 3 ? 1 : 0;
   constexpr int f1 = S * e1, f2 = S * e2, f3 = S * e3;
   const int rho = c.ax[0], nu = c.ax[J];
   const int pair = rho < nu ? pair_index(rho, nu) : pair_index(nu, rho);
-  const T sigma = T(S * (rho < nu ? 1 : -1));
-  su3<T> a, d;
-  if constexpr (S > 0) {
-    a = c.template u<1, 0, 0, 0, J>();
-    d = dagger(c.template u<0, 0, 0, 0, J>());
-  } else {
-    a = dagger(c.template u<1, -e1, -e2, -e3, J>());
-    d = c.template u<0, -e1, -e2, -e3, J>();
+  su3<T> ab, ax;
+  {
+    const su3<T> ub = c.template u<0, f1, f2, f3, 0>();  // b = ub^dagger
+    su3<T> x = mul<false, true>(c.template k<1, f1, f2, f3>(pair), ub);
+    mac<true, false>(x, ub, c.template k<0, f1, f2, f3>(pair));  // K2 b + b K3
+    su3<T> a;
+    if constexpr (S > 0)
+      a = c.template u<1, 0, 0, 0, J>();
+    else
+      a = dagger(c.template u<1, -e1, -e2, -e3, J>());
+    ab = mul<false, true>(a, ub);
+    ax = mul<false, false>(a, x);
   }
-  const su3<T> b = dagger(c.template u<0, f1, f2, f3, 0>());
-  const su3<T> abd = mul<false, false>(mul<false, false>(a, b), d);
-  su3<T> t = mul<false, false>(abd, c.template k<0, 0, 0, 0>(pair));
-  mac<false, false>(t, c.template k<1, 0, 0, 0>(pair), abd);
-  // a K2 b d + a b K3 d = a (K2 b + b K3) d
-  su3<T> x = mul<false, false>(c.template k<1, f1, f2, f3>(pair), b);
-  mac<false, false>(x, b, c.template k<0, f1, f2, f3>(pair));
-  mac<false, false>(t, mul<false, false>(a, x), d);
-  axpy(acc, sigma, t);
+  __builtin_amdgcn_sched_barrier(0);
+  su3<T> d;
+  if constexpr (S > 0)
+    d = dagger(c.template u<0, 0, 0, 0, J>());
+  else
+    d = c.template u<0, -e1, -e2, -e3, J>();
+  if constexpr (S > 0) {
+    w = mul<false, false>(ab, d);
+    t = mul<false, false>(ax, d);
+  } else {
+    mac_neg(w, ab, d);
+    mac_neg(t, ax, d);
+  }
 }
 
-// FP32: three waves per SIMD (168 VGPRs, 32 bytes of spills) instead of two at 175:
-// 1.78 -> 1.70 ms at 32^3 x 64. FP64 keeps one wave (256 VGPRs and 93 AGPRs; two waves
-// would spill 360 bytes).
+// acc += sum over s of sigma (abd K0 + K1 abd + a K2 bd + ab K3 d) for the two plaquettes in
+// the (rho, nu) plane, nu = ax[J], sigma = s (rho < nu ? 1 : -1). Both have the insertions
+// K0, K1 of the link's own ends, so these act once on the difference w of the two abd. The
+// plane is summed by itself before it is added to acc (in FP32 the error against 64 bits is
+// then no larger than with each plaquette summed by itself).
+template <int J, typename T>
+__device__ __forceinline__ void clover_plane(su3<T>& acc, const WCtx<T>& c0) {
+  su3<T> t, w;
+  clover_plaquette<J, 1>(t, w, c0);
+  __builtin_amdgcn_sched_barrier(0);
+  clover_plaquette<J, -1>(t, w, c0);
+  __builtin_amdgcn_sched_barrier(0);
+  WCtx<T> c = c0;
+  asm volatile("" : "+s"(c.U), "+s"(c.K));
+  const int rho = c.ax[0], nu = c.ax[J];
+  const int pair = rho < nu ? pair_index(rho, nu) : pair_index(nu, rho);
+  mac<false, false>(t, w, c.template k<0, 0, 0, 0>(pair));
+  mac<false, false>(t, c.template k<1, 0, 0, 0>(pair), w);
+  axpy(acc, T(rho < nu ? 1 : -1), t);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// FP32: two waves per SIMD (199 VGPRs); three would spill: 1.75 against 1.50 ms at
+// 32^3 x 64. FP64: one wave (256 VGPRs and 162 AGPRs). With one sum over s per plane and
+// projected spinors, FP32 1.63 -> 1.50 ms at 32^3 x 64, FP64 1.06 -> 0.95 ms at 24^3 x 48.
+// (abd as two rows with the third rebuilt would save another 2%, at an error against 64 bits
+// that is no longer below that of the separate plaquettes.)
 template <typename T>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : 1))) void wilson_force_kernel(Geom g, const T* __restrict__ U,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1))) void wilson_force_kernel(Geom g, const T* __restrict__ U,
                                                                const T* __restrict__ X, const T* __restrict__ Y,
                                                                const T* __restrict__ K, T* __restrict__ out,
                                                                double kappa, double csw, int ntiles) {
@@ -342,33 +447,25 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
   su3<T> acc;
   set_zero(acc);
   if (csw != 0.0) {
-    clover_plaquette<1, 1>(acc, c);
-    __builtin_amdgcn_sched_barrier(0);
-    clover_plaquette<1, -1>(acc, c);
-    __builtin_amdgcn_sched_barrier(0);
-    clover_plaquette<2, 1>(acc, c);
-    __builtin_amdgcn_sched_barrier(0);
-    clover_plaquette<2, -1>(acc, c);
-    __builtin_amdgcn_sched_barrier(0);
-    clover_plaquette<3, 1>(acc, c);
-    __builtin_amdgcn_sched_barrier(0);
-    clover_plaquette<3, -1>(acc, c);
-    __builtin_amdgcn_sched_barrier(0);
+    clover_plane<1>(acc, c);
+    clover_plane<2>(acc, c);
+    clover_plane<3>(acc, c);
   }
   // M = U (-2 kappa B' + w acc) + 2 kappa C' U^+, w = -c_sw kappa / 8
   const int pr = lt.p ^ 1;
   const int cbr = nbr_cb<1, 0, 0, 0>(c.nb);
-  const spinor<T> xk = load_spinor(X, lt.p, g.Vh, cb), yk = load_spinor(Y, lt.p, g.Vh, cb);
-  const spinor<T> xr = load_spinor(X, pr, g.Vh, cbr), yr = load_spinor(Y, pr, g.Vh, cbr);
-  const su3<T> Bp = outer(project(rho, -1, xr), yk);
-  const su3<T> Cp = outer(xk, project(rho, 1, yr));
   const T w = T(-csw * kappa / 8.0), mk = T(-2.0 * kappa);
   su3<T> inner;
+  {
+    const su3<T> Bp = outer(load_projected(X, pr, g.Vh, cbr, rho, T(-1)), load_projected(Y, lt.p, g.Vh, cb, rho, T(-1)));
 #pragma unroll
-  for (int e = 0; e < 9; ++e) {
-    inner.e[e].re = fma(mk, Bp.e[e].re, w * acc.e[e].re);
-    inner.e[e].im = fma(mk, Bp.e[e].im, w * acc.e[e].im);
+    for (int e = 0; e < 9; ++e) {
+      inner.e[e].re = fma(mk, Bp.e[e].re, w * acc.e[e].re);
+      inner.e[e].im = fma(mk, Bp.e[e].im, w * acc.e[e].im);
+    }
   }
+  __builtin_amdgcn_sched_barrier(0);
+  const su3<T> Cp = outer(load_projected(X, lt.p, g.Vh, cb, rho, T(1)), load_projected(Y, pr, g.Vh, cbr, rho, T(1)));
   const su3<T> u = c.template u<0, 0, 0, 0, 0>();
   su3<T> M = mul<false, false>(u, inner);
   su3<T> cu = mul<false, true>(Cp, u);
