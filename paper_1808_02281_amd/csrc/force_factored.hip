@@ -23,7 +23,7 @@ __global__ __launch_bounds__(factored_links<T>()) void force_factored_kernel(Geo
                                                                              double* __restrict__ partials, Coeffs cf,
                                                                              int ntiles) {
   constexpr int N = factored_links<T>();
-  const LinkTile lt = link_tile(g, blockIdx.x, ntiles, kBlock / N);
+  const LinkTile lt = force_tile(g, blockIdx.x, ntiles, N);
   const int cb = lt.chunk * N + threadIdx.x;
   double a[3] = {0.0, 0.0, 0.0};
   if (cb < g.Vh) factored_link<T, MODE>(g, U, S8, out, kick, cf, lt.mu, lt.p, cb, a);

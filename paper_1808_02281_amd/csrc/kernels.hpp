@@ -8,7 +8,7 @@
 
 namespace sym {
 
-constexpr int kBlock = 256;  // threads per workgroup for the per-link kernels
+constexpr int kBlock = kTileSites;  // threads per workgroup for the per-link kernels
 
 // Coefficients of the three loop classes and beta (eq. 18_3_27_30, eq. 18_6_4_1).
 struct Coeffs {

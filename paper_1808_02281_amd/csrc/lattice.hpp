@@ -210,6 +210,8 @@ struct LinkTile {
   int mu, p, chunk;
 };
 
+constexpr int kTileSites = 256;  // sites of the chunks that Geom::cps counts
+
 // split: the number of chunks of the launch's workgroup size per 256-site chunk (1, 2 or
 // 4 for 256, 128 or 64 links per workgroup); g.cps counts 256-site chunks.
 __device__ __forceinline__ LinkTile link_tile(const Geom& g, int linear, int ntiles, int split = 1) {
@@ -224,6 +226,41 @@ __device__ __forceinline__ LinkTile link_tile(const Geom& g, int linear, int nti
     chunk = (xcd * g.tslab + j % g.tslab) * (g.cps * split) + j / g.tslab;
   }
   r.chunk = chunk;
+  return r;
+}
+
+// Tiles of the factored force pass, n links per workgroup. What bounds the pass is staple
+// data from beyond an XCD's 4 MiB of L2 (15 GB fetched in FP32 and 34 GB in FP64 at
+// 32^3 x 64, of 2.8 and 5.6 GB of links and staples, at 6 to 7 TB/s). The chunks in flight
+// alone touch more than the L2 holds, so what helps is that they form a compact block,
+// whose matrices are used by the neighbours' waves at about the same time: about 16 chunks
+// (times 8 directions and parities) are in flight on an XCD, and the walk is z in fours
+// fastest, then t through the XCD's slab of ceil(Lt/8) slices, then the blocks of four z,
+// then y. At 32^3 x 64, against t fastest over the slab and then y and z (link_tile):
+// FP32 2.33 -> 2.11 ms, FP64 4.95 -> 4.34 ms. That needs chunks that lie in one (x, y) plane;
+// where a plane is not whole chunks the z-neighbours of a chunk straddle two others, and
+// the same walk over rounded plane sizes was slower (24^3 x 48: FP64 1.51 -> 1.89 ms, FP32
+// 0.70 -> 0.71 ms): such lattices keep link_tile.
+__device__ __forceinline__ LinkTile force_tile(const Geom& g, int linear, int ntiles, int n) {
+  const int plane = g.Lxh * g.L[1];
+  if (plane % n != 0) return link_tile(g, linear, ntiles, kTileSites / n);
+  const int tile = xcd_tile(linear, ntiles);
+  LinkTile r;
+  r.mu = tile & 3;
+  r.p = (tile >> 2) & 1;
+  const int Ly = plane / n, Lz = g.L[2], Lt = g.L[3];  // chunks along y, z, t
+  const int slab = (Lt + 7) >> 3;
+  int k = tile >> 3;
+  const int t0 = k / (slab * Lz * Ly) * slab;
+  const int tn = min(slab, Lt - t0);
+  k -= t0 * Lz * Ly;
+  const int y = k / (Lz * tn);
+  k -= y * Lz * tn;
+  const int z0 = k / (4 * tn) * 4;
+  const int zn = min(4, Lz - z0);
+  k -= z0 * tn;
+  const int t = k / zn, z = k - t * zn;
+  r.chunk = y + Ly * (z0 + z + Lz * (t0 + t));
   return r;
 }
 
