@@ -316,6 +316,7 @@ struct StapleStep {
   static constexpr int MU = fwd ? (K < 3 ? 0 : (K < 5 ? 1 : 2)) : (J < A ? J : J + 1);
 };
 constexpr int kStapleSteps = 18;
+static_assert(kStapleSteps == kStapleRoles, "one wave per step on small lattices");
 
 // What one step loads: the two links besides the site's own, and, with the first step
 // of a backward group (J = 0), w_A = U_{x-A,A}. The site's own u_a stay in registers
@@ -390,10 +391,32 @@ __device__ __forceinline__ void staple_pipe(const SCtx<T>& c, const Rows2<T> (&u
   }
 }
 
-// Pass 1 for site (p, cb) of lattice g: the 24 staples of its four links into S8
-// (POL: cache policy of the stores).
-template <typename T, int POL = kStoreNT>
-__device__ __forceinline__ void staples_site(const Geom& g, const T* U, T* S8, int p, int cb) {
+// Step `role` (0..17, wave-uniform) of the staples alone, for small lattices: a wave per
+// step instead of a wave for all of them, whose serial stream of loads and products takes
+// 17 us on any lattice that does not fill the GPU (4^4: 17 -> 7 us).
+template <int K, typename T>
+__device__ __forceinline__ void staple_one(const SCtx<T>& c, int role) {
+  if constexpr (K < kStapleSteps) {
+    if (role == K) {
+      using St = StapleStep<K>;
+      constexpr int MU = St::MU, A = St::A;
+      const StepData<T> d = load_step<K>(c);
+      Rows2<T> u[4], w = d.w;
+      if constexpr (St::fwd) {
+        u[MU] = c.template link<MU, 0, 0, 0, 0>();
+        u[A] = c.template link<A, 0, 0, 0, 0>();
+      } else if constexpr (St::J != 0) {
+        w = c.template link<A, -unit(0, A), -unit(1, A), -unit(2, A), -unit(3, A)>();
+      }
+      use_step<K, kStoreNT>(c, u, w, d);
+      return;
+    }
+    staple_one<K + 1>(c, role);
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ SCtx<T> site_ctx(const Geom& g, const T* U, T* S8, int p, int cb) {
   int x[4];
   cb_coords(g, p, cb, x);
   SCtx<T> c;
@@ -404,6 +427,14 @@ __device__ __forceinline__ void staples_site(const Geom& g, const T* U, T* S8, i
   c.p = p;
   c.cb = cb;
   make_nbr(g, x, c.nb);
+  return c;
+}
+
+// Pass 1 for site (p, cb) of lattice g: the 24 staples of its four links into S8
+// (POL: cache policy of the stores).
+template <typename T, int POL = kStoreNT>
+__device__ __forceinline__ void staples_site(const Geom& g, const T* U, T* S8, int p, int cb) {
+  const SCtx<T> c = site_ctx(g, U, S8, p, cb);
   Rows2<T> u[4];
   u[0] = c.template link<0, 0, 0, 0, 0>();
   u[1] = c.template link<1, 0, 0, 0, 0>();
@@ -472,6 +503,27 @@ struct FState {
   int Vh, mu, p, cb;
 };
 
+template <typename T>
+struct ShortLinks {
+  Rows2<T> lnk, uxm;
+};
+
+// U_{x,a} and U_{x+mu,a}, or U_{x-a,a} and U_{x+mu-a,a}, for e_F = +-a
+template <int F, typename T>
+__device__ __forceinline__ ShortLinks<T> load_links(const FCtx<T>& c) {
+  constexpr int fa = e_axis(F), fs = e_sign(F);
+  constexpr int f1 = fs * comp(1, fa), f2 = fs * comp(2, fa), f3 = fs * comp(3, fa);
+  ShortLinks<T> d;
+  if constexpr (fs > 0) {
+    d.lnk = c.template link_rows<0, 0, 0, 0, fa>();
+    d.uxm = c.template link_rows<1, 0, 0, 0, fa>();
+  } else {
+    d.lnk = c.template link_rows<0, f1, f2, f3, fa>();
+    d.uxm = c.template link_rows<1, f1, f2, f3, fa>();
+  }
+  return d;
+}
+
 template <int S, typename T>
 __device__ __forceinline__ auto load_fstep(const FCtx<T>& c0) {
   FCtx<T> c = c0;
@@ -505,13 +557,9 @@ __device__ __forceinline__ auto load_fstep(const FCtx<T>& c0) {
     } else {
       Short<T> d;
       d.see = c.template stap_rows<0, f1, f2, f3, 0, fa, fs>();
-      if constexpr (fs > 0) {
-        d.lnk = c.template link_rows<0, 0, 0, 0, fa>();
-        d.uxm = c.template link_rows<1, 0, 0, 0, fa>();
-      } else {
-        d.lnk = c.template link_rows<0, f1, f2, f3, fa>();
-        d.uxm = c.template link_rows<1, f1, f2, f3, fa>();
-      }
+      const ShortLinks<T> l = load_links<F>(c);
+      d.lnk = l.lnk;
+      d.uxm = l.uxm;
       return d;
     }
   } else {
@@ -519,6 +567,20 @@ __device__ __forceinline__ auto load_fstep(const FCtx<T>& c0) {
     d.u = c.template link_rows<0, 0, 0, 0, 0>();
     return d;
   }
+}
+
+// The inner factors of f = e_F: R = c_R S(x+f,mu,f) U_{x+f,-f} + c_C QA_f, and QB_f times c_C.
+template <int F, typename T>
+__device__ __forceinline__ su3<T> short_side(FState<T>& st, const Short<T>& d, const su3<T>& lnk) {
+  su3<T> R = full(rows_mul<(e_sign(F) > 0)>(d.see, lnk));  // S(x+f,mu,f) U_{x+f,-f}
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    R.e[i].re = fma(st.cC, st.QA.e[i].re, st.cR * R.e[i].re);
+    R.e[i].im = fma(st.cC, st.QA.e[i].im, st.cR * R.e[i].im);
+    st.QB.e[i].re *= st.cC;
+    st.QB.e[i].im *= st.cC;
+  }
+  return R;
 }
 
 template <int S, ForceOut MODE, typename T, typename D>
@@ -575,14 +637,7 @@ __device__ __forceinline__ void use_fstep(FState<T>& st, const D& d) {
       }
     } else {
       const su3<T> lnk = full(d.lnk), uxm = full(d.uxm);
-      su3<T> R = full(rows_mul<(fs > 0)>(d.see, lnk));  // S(x+f,mu,f) U_{x+f,-f}
-#pragma unroll
-      for (int i = 0; i < 9; ++i) {
-        R.e[i].re = fma(st.cC, st.QA.e[i].re, st.cR * R.e[i].re);
-        R.e[i].im = fma(st.cC, st.QA.e[i].im, st.cR * R.e[i].im);
-        st.QB.e[i].re *= st.cC;
-        st.QB.e[i].im *= st.cC;
-      }
+      const su3<T> R = short_side<F>(st, d, lnk);
       if constexpr (fs > 0) {
         mac<false, false>(st.t, uxm, R);
         mac<false, true>(st.t, st.QB, lnk);
@@ -632,20 +687,17 @@ __device__ __forceinline__ void force_pipe(const FCtx<T>& c, FState<T>& st, cons
   }
 }
 
-// Pass 2 for link (mu, p, cb): force epilogue per MODE, deficit partials into a[3].
-template <typename T, ForceOut MODE>
-__device__ __forceinline__ void factored_link(const Geom& g, const T* U, const T* S8, T* out, double kick,
-                                              const Coeffs& cf, int mu, int p, int cb, double a[3]) {
+template <typename T>
+__device__ __forceinline__ void link_state(const Geom& g, const T* U, const T* S8, T* out, double kick,
+                                           const Coeffs& cf, int mu, int p, int cb, FCtx<T>& c, FState<T>& st) {
   int x[4];
   cb_coords(g, p, cb, x);
-  FCtx<T> c;
   c.U = U;
   c.S8 = S8;
   c.Vh = g.Vh;
   c.Ss = s8_stride(g);
   c.p = p;
   make_frame(g, mu, x, c.axis, c.nb);
-  FState<T> st;
   st.cP = T(cf.c[0]);
   st.cR = T(cf.c[1]);
   st.cC = T(cf.c[2]);
@@ -656,12 +708,278 @@ __device__ __forceinline__ void factored_link(const Geom& g, const T* U, const T
   st.mu = mu;
   st.p = p;
   st.cb = cb;
+}
+
+// Pass 2 for link (mu, p, cb): force epilogue per MODE, deficit partials into a[3].
+template <typename T, ForceOut MODE>
+__device__ __forceinline__ void factored_link(const Geom& g, const T* U, const T* S8, T* out, double kick,
+                                              const Coeffs& cf, int mu, int p, int cb, double a[3]) {
+  FCtx<T> c;
+  FState<T> st;
+  link_state(g, U, S8, out, kick, cf, mu, p, cb, c, st);
   const auto d0 = load_fstep<0>(c);
   SYM_FENCE();
   force_pipe<0, MODE>(c, st, d0);
   a[0] = st.a[0];
   a[1] = st.a[1];
   a[2] = st.a[2];
+}
+
+// ------------------------------------------------- pass 2 on small lattices
+// On a small lattice one wave per 64 links leaves most SIMDs empty and the others with a
+// serial stream of 8,160 VALU instructions, 14 us of issue time whatever the lattice. Here
+// a workgroup of eight waves shares 64 links (one per lane of every wave), with the
+// intermediate matrices in LDS:
+//   phase 1  waves 0..5: the inner factors R_f and QB_f of direction f (items of the
+//            pipeline above, independent of each other); wave 6: tP and RA; wave 7: RB;
+//   phase 2  waves 0..2: row i of the long-side sum, of t and of its outer products, which
+//            need only row i of their left factors;
+//   phase 3  wave 0: B = U t and the epilogue.
+// Every matrix element goes through the same operations in the same order as in
+// factored_link, so the force is bitwise the same. Force pass, 4^4: FP32 22 -> 13 us, FP64
+// 24 -> 16 us; the whole force with action 38 -> 24 us and 42 -> 24 us.
+constexpr int kSmallWaves = 8;
+enum SmallSlot { kSlotR = 0, kSlotQB = 6, kSlotTP = 12, kSlotRA, kSlotRB, kSlotWR, kSlotT, kSmallSlots };
+
+template <typename T>
+constexpr size_t small_lds_bytes() {
+  return (size_t)kSmallSlots * 18 * 64 * sizeof(T);
+}
+
+template <typename T>
+struct LdsMats {
+  T* base;  // [slot][18][64]
+  int lane;
+
+  __device__ __forceinline__ void put(int slot, const su3<T>& m) const {
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      base[(slot * 18 + 2 * e) * 64 + lane] = m.e[e].re;
+      base[(slot * 18 + 2 * e + 1) * 64 + lane] = m.e[e].im;
+    }
+  }
+  __device__ __forceinline__ cx<T> elem_at(int slot, int e) const {
+    return cx<T>{base[(slot * 18 + 2 * e) * 64 + lane], base[(slot * 18 + 2 * e + 1) * 64 + lane]};
+  }
+  __device__ __forceinline__ su3<T> get(int slot) const {
+    su3<T> m;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) m.e[e] = elem_at(slot, e);
+    return m;
+  }
+};
+
+template <typename T>
+struct Row {
+  cx<T> e[3];
+};
+
+// Row I of A^{DA} B^{DB}, and the same accumulated, with the operations of mul and mac.
+template <bool DA, bool DB, typename T>
+__device__ __forceinline__ Row<T> row_mul(const cx<T> (&x)[3], const su3<T>& b) {
+  Row<T> r;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    cx<T> y = elem<DB>(b, 0, j);
+    T re = x[0].re * y.re;
+    T im = x[0].re * y.im;
+    re = fma(-x[0].im, y.im, re);
+    im = fma(x[0].im, y.re, im);
+#pragma unroll
+    for (int k = 1; k < 3; ++k) {
+      y = elem<DB>(b, k, j);
+      re = fma(x[k].re, y.re, re);
+      im = fma(x[k].re, y.im, im);
+      re = fma(-x[k].im, y.im, re);
+      im = fma(x[k].im, y.re, im);
+    }
+    r.e[j] = cx<T>{re, im};
+  }
+  return r;
+}
+
+template <bool DB, typename T>
+__device__ __forceinline__ void row_mac(Row<T>& r, const cx<T> (&x)[3], const su3<T>& b) {
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    T re = r.e[j].re, im = r.e[j].im;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const cx<T> y = elem<DB>(b, k, j);
+      re = fma(x[k].re, y.re, re);
+      im = fma(x[k].re, y.im, im);
+      re = fma(-x[k].im, y.im, re);
+      im = fma(x[k].im, y.re, im);
+    }
+    r.e[j] = cx<T>{re, im};
+  }
+}
+
+// Phase 1, waves 0..5.
+template <int F, typename T>
+__device__ __forceinline__ void small_inner(const FCtx<T>& c, FState<T>& st, const LdsMats<T>& m, int role) {
+  if constexpr (F < 6) {
+    if (role == F) {
+      const auto d0 = load_fstep<7 + 3 * F>(c);
+      const auto d1 = load_fstep<8 + 3 * F>(c);
+      SYM_FENCE();
+      use_fstep<7 + 3 * F, ForceOut::Store>(st, d0);
+      const auto d2 = load_fstep<9 + 3 * F>(c);
+      SYM_FENCE();
+      use_fstep<8 + 3 * F, ForceOut::Store>(st, d1);
+      SYM_FENCE();
+      m.put(kSlotR + F, short_side<F>(st, d2, full(d2.lnk)));
+      m.put(kSlotQB + F, st.QB);
+      return;
+    }
+    small_inner<F + 1>(c, st, m, role);
+  }
+}
+
+// Phase 1, waves 6 (RB = false: tP and RA) and 7 (RB), steps S..5 with the loads of the
+// next step requested before the current one is used.
+template <int S, bool RB, typename T>
+struct LongPair {
+  Rows2<T> sx, o;
+};
+template <int S, bool RB, typename T>
+__device__ __forceinline__ LongPair<S, RB, T> load_long(const FCtx<T>& c0) {
+  FCtx<T> c = c0;
+  launder(c);
+  constexpr int a = e_axis(S), s = e_sign(S);
+  LongPair<S, RB, T> d;
+  d.sx = c.template stap_rows<0, 0, 0, 0, 0, a, s>();
+  d.o = c.template stap_rows<(RB ? -1 : 1), 0, 0, 0, 0, a, s>();
+  return d;
+}
+template <int S, bool RB, typename T>
+__device__ __forceinline__ void small_long(const FCtx<T>& c, FState<T>& st, const LongPair<S, RB, T>& d) {
+  const su3<T> sx = full(d.sx);
+  auto use = [&] {
+    if constexpr (RB) {
+      if constexpr (S == 0)
+        st.RB = mul<false, false>(sx, full(d.o));
+      else
+        mac<false, false>(st.RB, sx, full(d.o));
+    } else {
+      const su3<T> ra = full(rows_mul<false>(d.o, sx));
+      if constexpr (S == 0) {
+        st.tP = sx;
+        st.RA = ra;
+      } else {
+        add(st.tP, sx);
+        add(st.RA, ra);
+      }
+    }
+  };
+  if constexpr (S < 5) {
+    const auto n = load_long<S + 1, RB>(c);
+    SYM_FENCE();
+    use();
+    SYM_FENCE();
+    small_long<S + 1, RB>(c, st, n);
+  } else {
+    use();
+  }
+}
+
+// Phase 2, row I of t: the outer products of f = e_F.. in order.
+template <int I, bool D, typename T>
+__device__ __forceinline__ void take_row(cx<T> (&x)[3], const su3<T>& a) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] = elem<D>(a, I, k);
+}
+template <int F, int I, typename T>
+__device__ __forceinline__ void small_outer(const FCtx<T>& c, Row<T>& t, const LdsMats<T>& m, const Rows2<T>& lr,
+                                            const Rows2<T>& ur) {
+  const su3<T> lnk = full(lr), uxm = full(ur);
+  Rows2<T> ln = lr, un = ur;
+  if constexpr (F < 5) {
+    const auto d = load_links<F + 1>(c);
+    ln = d.lnk;
+    un = d.uxm;
+  }
+  SYM_FENCE();
+  cx<T> x[3];
+  take_row<I, (e_sign(F) < 0)>(x, uxm);
+  row_mac<false>(t, x, m.get(kSlotR + F));
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] = m.elem_at(kSlotQB + F, 3 * I + k);
+  row_mac<(e_sign(F) > 0)>(t, x, lnk);
+  SYM_FENCE();
+  if constexpr (F < 5) small_outer<F + 1, I>(c, t, m, ln, un);
+}
+
+template <int I, typename T>
+__device__ __forceinline__ void small_row(const FCtx<T>& c, const FState<T>& st, const LdsMats<T>& m) {
+  const auto d = load_fstep<6>(c);
+  const auto l0 = load_links<0>(c);
+  cx<T> x[3];
+  take_row<I, false>(x, full(d.up));
+  Row<T> w = row_mul<false, false>(x, m.get(kSlotRA));  // U_{x+mu,mu} RA
+#pragma unroll
+  for (int k = 0; k < 3; ++k) x[k] = m.elem_at(kSlotRB, 3 * I + k);
+  row_mac<false>(w, x, full(d.um));                      // + RB U_{x-mu,mu}
+  Row<T> t;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const cx<T> p = m.elem_at(kSlotTP, 3 * I + j);
+    t.e[j].re = fma(st.cP, p.re, st.cR * w.e[j].re);
+    t.e[j].im = fma(st.cP, p.im, st.cR * w.e[j].im);
+    m.base[(kSlotWR * 18 + 6 * I + 2 * j) * 64 + m.lane] = w.e[j].re;
+    m.base[(kSlotWR * 18 + 6 * I + 2 * j + 1) * 64 + m.lane] = w.e[j].im;
+  }
+  small_outer<0, I>(c, t, m, l0.lnk, l0.uxm);
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    m.base[(kSlotT * 18 + 6 * I + 2 * j) * 64 + m.lane] = t.e[j].re;
+    m.base[(kSlotT * 18 + 6 * I + 2 * j + 1) * 64 + m.lane] = t.e[j].im;
+  }
+}
+
+// One wave's part of link (mu, p, cb): `wave` is wave-uniform, `active` false for lanes past
+// the lattice (they only take part in the barriers). a[3] is set by wave 0's active lanes.
+template <typename T, ForceOut MODE>
+__device__ __forceinline__ void factored_link_small(const Geom& g, const T* U, const T* S8, T* out, double kick,
+                                                    const Coeffs& cf, int mu, int p, int cb, bool active, int wave,
+                                                    const LdsMats<T>& m, double a[3]) {
+  FCtx<T> c;
+  FState<T> st;
+  link_state(g, U, S8, out, kick, cf, mu, p, cb, c, st);
+  if (active) {
+    if (wave < 6) {
+      small_inner<0>(c, st, m, wave);
+    } else if (wave == 6) {
+      small_long<0, false>(c, st, load_long<0, false>(c));
+      m.put(kSlotTP, st.tP);
+      m.put(kSlotRA, st.RA);
+    } else {
+      small_long<0, true>(c, st, load_long<0, true>(c));
+      m.put(kSlotRB, st.RB);
+    }
+  }
+  __syncthreads();
+  if (active) {
+    if (wave == 0)
+      small_row<0>(c, st, m);
+    else if (wave == 1)
+      small_row<1>(c, st, m);
+    else if (wave == 2)
+      small_row<2>(c, st, m);
+  }
+  __syncthreads();
+  if (active && wave == 0) {
+    const auto d = load_fstep<kSteps - 1>(c);
+    const su3<T> u = full(d.u);
+    st.a[0] = 18.0 - re_tr_mul(u, m.get(kSlotTP));
+    st.a[1] = 36.0 - re_tr_mul(u, m.get(kSlotWR));
+    st.part = double(st.cP) * (18.0 - st.a[0]) + double(st.cR) * (36.0 - st.a[1]);
+    st.t = m.get(kSlotT);
+    use_fstep<kSteps - 1, MODE>(st, d);
+    a[0] = st.a[0];
+    a[1] = st.a[1];
+    a[2] = st.a[2];
+  }
 }
 
 }  // namespace factored

@@ -51,9 +51,24 @@ template <typename T>
 constexpr int factored_links() {
   return sizeof(T) == 4 ? 128 : 64;
 }
+// Lattices on which the staple and force passes split a site's or a link's work over waves
+// (see the small-lattice kernels in force_factored.hip). The split costs work (18 loads of a
+// site's own links, phases that wait), so it pays while it only fills empty SIMDs:
+//   staples, a wave per 64 sites and step: while all these waves are resident, 6 per SIMD
+//     in FP32 and 3 in FP64 on 1024 SIMDs. FP32 12^4 (5,832 waves) 20 -> 12 us, 16^4
+//     (18,432) 21 -> 29 us; FP64 8^3 x 16 (2,304) 21 -> 11 us, 12^4 22 -> 20 us, 16^4 39 -> 53 us;
+//   force, eight waves per 64 links: while every workgroup has a CU of its own. 8^4 (256
+//     workgroups) FP32 22 -> 15 us, FP64 25 -> 20 us; 8^3 x 16 23 -> 26 and 27 -> 35 us.
+constexpr int kCUs = 256;
+constexpr int kStapleRoles = 18;  // steps of a site's staples
+template <typename T>
+inline bool staples_are_small(const Geom& g) {
+  return 2ll * ((g.Vh + 63) / 64) * kStapleRoles <= 4 * kCUs * (sizeof(T) == 4 ? 6 : 3);
+}
+inline bool force_is_small(const Geom& g) { return link_tiles(g, 64) <= kCUs; }
 template <typename T>
 inline int factored_tiles(const Geom& g) {
-  return link_tiles(g, factored_links<T>());
+  return link_tiles(g, force_is_small(g) ? 64 : factored_links<T>());
 }
 // The most per-workgroup partials any force launch writes (workspace sizing).
 inline int max_force_tiles(const Geom& g) { return link_tiles(g, 64); }
