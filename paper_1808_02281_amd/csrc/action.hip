@@ -245,46 +245,82 @@ __global__ __launch_bounds__(256) void finish_stage1(const double* __restrict__ 
   block_sum_store<4>(v, stage + 4 * (size_t)blockIdx.x);
 }
 
-// Stage 2 (one block): with deficit sums w_X = sum over class-X loops of (3 - Re tr P),
+// S and W from the summed partials v: with deficit sums w_X = sum over class-X loops of
+// (3 - Re tr P),
 //   S = beta/3 (c_P w_P + c_R w_R + c_C w_C),  W_X = 3 n_X V - w_X  (n = 6, 12, 16).
 // mode 0 writes out[0..3] = S, W_P, W_R, W_C; mode 1 adds the kinetic partials and
 // writes out[0] = S + K.
+__device__ __forceinline__ void finish_values(const double (&v)[4], int kind, const Coeffs& c, double V, int mode,
+                                              double* __restrict__ out) {
+  double wP, wR, wC, cwC;
+  if (kind == 0) {  // direct force: each loop seen from 4 / 6 / 6 links
+    wP = v[0] / 4.0;
+    wR = v[1] / 6.0;
+    wC = v[2] / 6.0;
+    cwC = c.c[2] * wC;
+  } else if (kind == 1) {  // action kernel: per-loop sums
+    wP = v[0];
+    wR = v[1];
+    wC = v[2];
+    cwC = c.c[2] * wC;
+  } else {  // factored force: long sides see a rectangle 4 times, the mixed sum holds
+            // c_R x (2 views of every rectangle) + c_C x (6 views of every cube loop);
+            // W_C needs c_C != 0 (the library runs the action kernel otherwise)
+    wP = v[0] / 4.0;
+    wR = v[1] / 4.0;
+    cwC = (v[2] - 0.5 * c.c[1] * v[1]) / 6.0;
+    wC = c.c[2] != 0.0 ? cwC / c.c[2] : __builtin_nan("");
+  }
+  const double S = c.beta / 3.0 * (c.c[0] * wP + c.c[1] * wR + cwC);
+  if (mode == 0) {
+    out[0] = S;
+    out[1] = 18.0 * V - wP;
+    out[2] = 36.0 * V - wR;
+    out[3] = 48.0 * V - wC;
+  } else {
+    out[0] = S + v[3];
+  }
+}
+
+// Stage 2 (one block).
 __global__ __launch_bounds__(64) void finish_stage2(const double* __restrict__ stage, int kind, Coeffs c, double V,
                                                     int mode, double* __restrict__ out) {
   double v[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) v[k] = stage[4 * (size_t)threadIdx.x + k];
   block_sum<4>(v);
-  if (threadIdx.x == 0) {
-    double wP, wR, wC, cwC;
-    if (kind == 0) {  // direct force: each loop seen from 4 / 6 / 6 links
-      wP = v[0] / 4.0;
-      wR = v[1] / 6.0;
-      wC = v[2] / 6.0;
-      cwC = c.c[2] * wC;
-    } else if (kind == 1) {  // action kernel: per-loop sums
-      wP = v[0];
-      wR = v[1];
-      wC = v[2];
-      cwC = c.c[2] * wC;
-    } else {  // factored force: long sides see a rectangle 4 times, the mixed sum holds
-              // c_R x (2 views of every rectangle) + c_C x (6 views of every cube loop);
-              // W_C needs c_C != 0 (the library runs the action kernel otherwise)
-      wP = v[0] / 4.0;
-      wR = v[1] / 4.0;
-      cwC = (v[2] - 0.5 * c.c[1] * v[1]) / 6.0;
-      wC = c.c[2] != 0.0 ? cwC / c.c[2] : __builtin_nan("");
-    }
-    const double S = c.beta / 3.0 * (c.c[0] * wP + c.c[1] * wR + cwC);
-    if (mode == 0) {
-      out[0] = S;
-      out[1] = 18.0 * V - wP;
-      out[2] = 36.0 * V - wR;
-      out[3] = 48.0 * V - wC;
-    } else {
-      out[0] = S + v[3];
-    }
+  if (threadIdx.x == 0) finish_values(v, kind, c, V, mode, out);
+}
+
+// Both stages in one block, for the partials of small lattices (at most kFinishSmall: four
+// per thread): one launch less, 4 us of a 4^4 force's 28.
+constexpr int kFinishSmall = 1024;
+
+__global__ __launch_bounds__(256) void finish_small(const double* __restrict__ act, int nact,
+                                                    const double* __restrict__ kin, int nkin, int kind, Coeffs c,
+                                                    double V, int mode, double* __restrict__ out) {
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int i = threadIdx.x; i < nact; i += blockDim.x) {
+    v[0] += act[3 * (size_t)i + 0];
+    v[1] += act[3 * (size_t)i + 1];
+    v[2] += act[3 * (size_t)i + 2];
   }
+  for (int i = threadIdx.x; i < nkin; i += blockDim.x) v[3] += kin[i];
+  block_sum<4>(v);
+  if (threadIdx.x == 0) finish_values(v, kind, c, V, mode, out);
+}
+
+hipError_t finish(const double* act, int nact, const double* kin, int nkin, int kind, const Coeffs& c, double V,
+                  int mode, double* stage, double* out, hipStream_t s) {
+  if (nact <= kFinishSmall && nkin <= kFinishSmall) {
+    finish_small<<<1, 256, 0, s>>>(act, nact, kin, nkin, kind, c, V, mode, out);
+    return hipGetLastError();
+  }
+  finish_stage1<<<kFinishGroups, 256, 0, s>>>(act, nact, kin, nkin, stage);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  finish_stage2<<<1, kFinishGroups, 0, s>>>(stage, kind, c, V, mode, out);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -303,21 +339,13 @@ template hipError_t launch_action<double>(const Geom&, const double*, double*, h
 
 hipError_t launch_finish_action(const double* partials, int nparts, int kind, const Geom& g, const Coeffs& c,
                                 double* stage, double* out, hipStream_t s) {
-  finish_stage1<<<kFinishGroups, 256, 0, s>>>(partials, nparts, nullptr, 0, stage);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  finish_stage2<<<1, kFinishGroups, 0, s>>>(stage, kind, c, 2.0 * g.Vh, 0, out);
-  return hipGetLastError();
+  return finish(partials, nparts, nullptr, 0, kind, c, 2.0 * g.Vh, 0, stage, out, s);
 }
 
 hipError_t launch_finish_hamiltonian(const double* act_parts, int nact, int act_kind, const double* kin_parts,
                                      int nkin, const Geom& g, const Coeffs& c, double* stage, double* out,
                                      hipStream_t s) {
-  finish_stage1<<<kFinishGroups, 256, 0, s>>>(act_parts, nact, kin_parts, nkin, stage);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  finish_stage2<<<1, kFinishGroups, 0, s>>>(stage, act_kind, c, 2.0 * g.Vh, 1, out);
-  return hipGetLastError();
+  return finish(act_parts, nact, kin_parts, nkin, act_kind, c, 2.0 * g.Vh, 1, stage, out, s);
 }
 
 }  // namespace sym
