@@ -161,8 +161,8 @@ int md_leapfrog(const int32_t L[4], double u0, double beta, int prec, void* U, v
  * per lattice. ws: at least sym_batch_workspace_bytes(n, L, prec) bytes (0 if invalid).
  * The schedule (number of persistent workgroups, or one workgroup per tile; tile order;
  * links per workgroup; occupancy cap) is the one sym_batch_autotune chose for these
- * shapes and precision in this process, else one workgroup of 256 links per tile in an
- * XCD-contiguous order at the occupancy of sym_force. Every schedule gives the same
+ * shapes and precision in this process, else one workgroup of 128 links per tile in an
+ * XCD-contiguous order without an occupancy cap. Every schedule gives the same
  * forces; the actions agree to rounding (the partial sums are grouped by workgroup).
  */
 size_t sym_batch_workspace_bytes(int n, const int32_t* L, int prec);
@@ -172,7 +172,7 @@ int sym_force_batch(int n, const int32_t* L, double u0, double beta, int prec, c
 /*
  * Autotuner for sym_force_batch: times (mean of 3 runs after a warm-up) every candidate
  * schedule of the force pass, 48 in all:
- *   links per workgroup {256, 128} x LDS reserved per workgroup {0, the sym_force default,
+ *   links per workgroup {256, 128} x LDS reserved per workgroup {0, 56 (FP32) or 96 (FP64) KiB,
  *   96 KiB (one workgroup per CU)}, which caps the resident waves per SIMD, x grid {one
  *   workgroup per tile (reported as 0), 2048, 1024, 512 persistent workgroups} x tile
  *   order {strided, XCD-contiguous},

@@ -266,7 +266,7 @@ def batch_autotune(Us, Ls, u0, beta, out=None):
     """Time the candidate schedules of force_batch for this batch (sym_batch_autotune);
     the best one is kept for later force_batch calls with the same lattice shapes.
     Returns (best, log): best = {grid, order, links, lds_kib} (grid 0 is one workgroup per
-    tile, lds_kib -1 the default occupancy), log = [(schedule dict, ms per batch), ...]
+    tile, lds_kib -1 for 56 KiB in FP32 and 96 in FP64), log = [(schedule dict, ms per batch), ...]
     for every candidate. ``out`` (optional, one field per lattice) receives the forces of
     the last schedule timed."""
     n, Lflat, prec = _batch_args(Us, Ls)

@@ -367,7 +367,8 @@ int batch_plan(int n, const int32_t* L, int prec, BatchPlan* plan) {
 //   order: tile order (0 strided, 1 XCD-contiguous, see BatchTable);
 //   links: links (threads) per workgroup, 256 or 128;
 //   lds_kib: dynamic LDS reserved per workgroup, capping the workgroups per CU (160 KiB
-//            of LDS) and hence the waves per SIMD; -1 = the single-lattice default.
+//            of LDS) and hence the waves per SIMD; -1 = 56 (FP32) or
+//            96 (FP64).
 struct Schedule {
   int grid;
   int order;
@@ -384,10 +385,12 @@ std::vector<int> tune_key(int n, const int32_t* L, int prec) {
 }
 
 Schedule default_schedule(int) {
-  // one workgroup of 256 links per tile, XCD-contiguous, the single-lattice occupancy:
-  // on 64 lattices from {8^4, 12^4, 16^3x32} (FP32) 4.43 ms, against 5.41 ms for 64
-  // single-lattice calls
-  return Schedule{0, 1, 256, -1};
+  // one workgroup of 128 links per tile, XCD-contiguous, as many as the registers allow
+  // (two waves per SIMD in FP32, one in FP64). Against workgroups of 256 links under an LDS
+  // cap, with the chunks of each lattice in order: 60 lattices from {8^4, 12^4, 16^3 x 32}
+  // FP32 4.32 -> 4.27 ms, FP64 8.91 -> 8.37 ms; 3 of 32^3 x 16 2.43 -> 2.22 and 4.94 -> 4.34 ms;
+  // 64 of 8^4 0.344 -> 0.333 and 0.663 -> 0.637 ms.
+  return Schedule{0, 1, 128, 0};
 }
 
 template <typename T>

@@ -60,6 +60,8 @@ __global__ __launch_bounds__(kBlock) void staples_batch_kernel(const BatchTable 
   }
 }
 
+constexpr int kBatchSlab = 8;
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void force_batch_kernel(const BatchTable b, double* __restrict__ partials,
                                                              Coeffs cf) {
@@ -70,7 +72,11 @@ __global__ __launch_bounds__(kBlock) void force_batch_kernel(const BatchTable b,
     const BatchEntry& e = b.e[find_lattice<false>(b, tile)];
     const Geom g = geom_of(e);
     const int local = tile - e.tile_begin;
-    const int cb = (local >> 3) * (int)blockDim.x + threadIdx.x;  // blockDim.x links per tile
+    // chunks in the walk of the single-lattice pass (over slabs of kBatchSlab t-slices) where
+    // the lattice's planes are whole chunks, else in order
+    const int links = (int)blockDim.x;  // per tile
+    const int chunk = planes_are_chunks(g, links) ? walk_chunk(g, links, kBatchSlab, local >> 3) : local >> 3;
+    const int cb = chunk * links + threadIdx.x;
     double a[3] = {0.0, 0.0, 0.0};
     if (cb < g.Vh)
       factored_link<T, ForceOut::Store>(g, static_cast<const T*>(e.U), static_cast<const T*>(e.S8),

@@ -72,7 +72,7 @@ inline int factored_tiles(const Geom& g) {
 }
 // The most per-workgroup partials any force launch writes (workspace sizing).
 inline int max_force_tiles(const Geom& g) { return link_tiles(g, 64); }
-// Dynamic LDS reserved by the batched force launch (default schedule) to cap resident
+// Dynamic LDS that a schedule of the batched force with lds_kib < 0 reserves to cap resident
 // workgroups of 256 links per CU (160 KiB of LDS per CU): 56 KiB -> 2 (FP32), 96 KiB -> 1
 // (FP64), which is where the registers put them anyway.
 template <typename T>
@@ -115,7 +115,7 @@ hipError_t launch_staples_batch(const BatchTable& b, int grid, hipStream_t s);
 template <typename T>
 // links: threads (links) per workgroup of the force pass, 256 or 128 (the table's link
 // tiles must have been counted with it); lds_kib: dynamic LDS reserved per workgroup, which
-// caps the resident workgroups per CU (negative: the single-lattice default).
+// caps the resident workgroups per CU (negative: factored_lds_reservation).
 hipError_t launch_force_batch(const BatchTable& b, int grid, int links, int lds_kib, double* partials,
                               const Coeffs& c, hipStream_t s);
 // One block per lattice: per-lattice action from the pass-2 partials (kind 2).

@@ -241,16 +241,11 @@ __device__ __forceinline__ LinkTile link_tile(const Geom& g, int linear, int nti
 // where a plane is not whole chunks the z-neighbours of a chunk straddle two others, and
 // the same walk over rounded plane sizes was slower (24^3 x 48: FP64 1.51 -> 1.89 ms, FP32
 // 0.70 -> 0.71 ms): such lattices keep link_tile.
-__device__ __forceinline__ LinkTile force_tile(const Geom& g, int linear, int ntiles, int n) {
-  const int plane = g.Lxh * g.L[1];
-  if (plane % n != 0) return link_tile(g, linear, ntiles, kTileSites / n);
-  const int tile = xcd_tile(linear, ntiles);
-  LinkTile r;
-  r.mu = tile & 3;
-  r.p = (tile >> 2) & 1;
-  const int Ly = plane / n, Lz = g.L[2], Lt = g.L[3];  // chunks along y, z, t
-  const int slab = (Lt + 7) >> 3;
-  int k = tile >> 3;
+__device__ __forceinline__ bool planes_are_chunks(const Geom& g, int n) { return g.Lxh * g.L[1] % n == 0; }
+
+// The chunk of n sites at position k of the walk (planes_are_chunks(g, n) holds).
+__device__ __forceinline__ int walk_chunk(const Geom& g, int n, int slab, int k) {
+  const int Ly = g.Lxh * g.L[1] / n, Lz = g.L[2], Lt = g.L[3];  // chunks along y, z, t
   const int t0 = k / (slab * Lz * Ly) * slab;
   const int tn = min(slab, Lt - t0);
   k -= t0 * Lz * Ly;
@@ -260,7 +255,16 @@ __device__ __forceinline__ LinkTile force_tile(const Geom& g, int linear, int nt
   const int zn = min(4, Lz - z0);
   k -= z0 * tn;
   const int t = k / zn, z = k - t * zn;
-  r.chunk = y + Ly * (z0 + z + Lz * (t0 + t));
+  return y + Ly * (z0 + z + Lz * (t0 + t));
+}
+
+__device__ __forceinline__ LinkTile force_tile(const Geom& g, int linear, int ntiles, int n) {
+  if (!planes_are_chunks(g, n)) return link_tile(g, linear, ntiles, kTileSites / n);
+  const int tile = xcd_tile(linear, ntiles);
+  LinkTile r;
+  r.mu = tile & 3;
+  r.p = (tile >> 2) & 1;
+  r.chunk = walk_chunk(g, n, (g.L[3] + 7) >> 3, tile >> 3);
   return r;
 }
 
