@@ -1,5 +1,5 @@
-// Wilson fermion force with clover term for given vectors X, Y: spinor layout
-// kernels, clover insertion kernel and the per-link force kernel.
+// Wilson fermion force with clover term for given vectors X, Y: clover insertion kernel and
+// the per-link force kernel.
 //
 // arXiv:1808.02281, Sec. "Wilson fermion action with clover term". With
 // D = A - kappa Dh (eq. 18_7_17_2), hopping part of eq. 18_7_17_4 and clover diagonal
@@ -473,33 +473,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
   store_link(block_ptr(out, rho, lt.p, g.Vh), g.Vh, cb, ta_scaled(M, T(-0.5)));
 }
 
-// canonical (Lt,Lz,Ly,Lx,4,3) complex <-> field[p][12][V/2]
-template <typename T, bool PACK>
-__global__ __launch_bounds__(kBlock) void spinor_layout_kernel(Geom g, const T* __restrict__ src,
-                                                                T* __restrict__ dst) {
-  const long long s = (long long)blockIdx.x * kBlock + threadIdx.x;
-  if (s >= 2ll * g.Vh) return;
-  int r = (int)s;
-  const int x = r % g.L[0];
-  r /= g.L[0];
-  const int y = r % g.L[1];
-  r /= g.L[1];
-  const int z = r % g.L[2];
-  const int t = r / g.L[2];
-  const int p = (x + y + z + t) & 1, cb = (int)(s >> 1);
-  const cx<T>* a = reinterpret_cast<const cx<T>*>(src);
-  cx<T>* b = reinterpret_cast<cx<T>*>(dst);
-#pragma unroll
-  for (int e = 0; e < 12; ++e) {
-    const size_t soa = (size_t)(p * 12 + e) * (size_t)g.Vh + cb;
-    const size_t aos = (size_t)s * 12 + e;
-    if constexpr (PACK)
-      b[soa] = a[aos];
-    else
-      b[aos] = a[soa];
-  }
-}
-
 }  // namespace
 
 template <typename T>
@@ -517,28 +490,15 @@ hipError_t launch_wilson_force(const Geom& g, const T* U, const T* X, const T* Y
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_spinor_layout(const Geom& g, const T* src, T* dst, bool pack, hipStream_t s) {
-  const long long n = 2ll * g.Vh;
-  const unsigned blocks = (unsigned)((n + kBlock - 1) / kBlock);
-  if (pack)
-    spinor_layout_kernel<T, true><<<blocks, kBlock, 0, s>>>(g, src, dst);
-  else
-    spinor_layout_kernel<T, false><<<blocks, kBlock, 0, s>>>(g, src, dst);
-  return hipGetLastError();
-}
-
 #ifndef SYM_ONLY_F64
 template hipError_t launch_wilson_clover<float>(const Geom&, const float*, const float*, float*, hipStream_t);
 template hipError_t launch_wilson_force<float>(const Geom&, const float*, const float*, const float*, const float*,
                                                float*, double, double, hipStream_t);
-template hipError_t launch_spinor_layout<float>(const Geom&, const float*, float*, bool, hipStream_t);
 #endif
 #ifndef SYM_ONLY_F32
 template hipError_t launch_wilson_clover<double>(const Geom&, const double*, const double*, double*, hipStream_t);
 template hipError_t launch_wilson_force<double>(const Geom&, const double*, const double*, const double*,
                                                 const double*, double*, double, double, hipStream_t);
-template hipError_t launch_spinor_layout<double>(const Geom&, const double*, double*, bool, hipStream_t);
 #endif
 
 }  // namespace sym
