@@ -24,13 +24,19 @@ __device__ __forceinline__ double block_max(double v) {
   return m;
 }
 
+// kCheckGrid workgroups loop over the tiles: a reduction and three partials per workgroup
+// instead of per tile, and few partials for the one finishing block. FP64 24^3 x 48 102 -> 93 us, FP32 32^3 x 64
+// 201 -> 167 us.
+constexpr int kCheckGrid = 2048;
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void check_links_kernel(Geom g, const T* __restrict__ U,
                                                              double* __restrict__ partials, int ntiles) {
-  const LinkTile lt = link_tile(g, blockIdx.x, ntiles);
-  const int cb = lt.chunk * kBlock + threadIdx.x;
   double unit = 0.0, det = 0.0, bad = 0.0;
-  if (cb < g.Vh) {
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const LinkTile lt = link_tile(g, tile, ntiles);
+    const int cb = lt.chunk * kBlock + threadIdx.x;
+    if (cb >= g.Vh) continue;
     const su3<T> u = load_link(block_ptr(U, lt.mu, lt.p, g.Vh), g.Vh, cb);
     su3<double> d;
     bool finite = true;
@@ -47,15 +53,15 @@ __global__ __launch_bounds__(kBlock) void check_links_kernel(Geom g, const T* __
         const double re = h.e[i].re - ((i % 4 == 0) ? 1.0 : 0.0);
         s += re * re + h.e[i].im * h.e[i].im;
       }
-      unit = sqrt(s);
+      unit = fmax(unit, sqrt(s));
       const cd m0 = cd{cm(d.e[4], d.e[8]).re - cm(d.e[5], d.e[7]).re, cm(d.e[4], d.e[8]).im - cm(d.e[5], d.e[7]).im};
       const cd m1 = cd{cm(d.e[3], d.e[8]).re - cm(d.e[5], d.e[6]).re, cm(d.e[3], d.e[8]).im - cm(d.e[5], d.e[6]).im};
       const cd m2 = cd{cm(d.e[3], d.e[7]).re - cm(d.e[4], d.e[6]).re, cm(d.e[3], d.e[7]).im - cm(d.e[4], d.e[6]).im};
       const cd a = cm(d.e[0], m0), b = cm(d.e[1], m1), c = cm(d.e[2], m2);
       const double dre = a.re - b.re + c.re - 1.0, dim = a.im - b.im + c.im;
-      det = sqrt(dre * dre + dim * dim);
+      det = fmax(det, sqrt(dre * dre + dim * dim));
     } else {
-      bad = 1.0;
+      bad += 1.0;
     }
   }
   unit = block_max(unit);
@@ -121,10 +127,11 @@ template hipError_t launch_reunitarise<double>(const Geom&, double*, hipStream_t
 template <typename T>
 hipError_t launch_check_links(const Geom& g, const T* U, double* partials, double* out, hipStream_t s) {
   const int nt = link_tiles(g);
-  check_links_kernel<T><<<nt, kBlock, 0, s>>>(g, U, partials, nt);
+  const int grid = nt < kCheckGrid ? nt : kCheckGrid;
+  check_links_kernel<T><<<grid, kBlock, 0, s>>>(g, U, partials, nt);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  check_finish_kernel<<<1, kBlock, 0, s>>>(partials, nt, out);
+  check_finish_kernel<<<1, kBlock, 0, s>>>(partials, grid, out);
   return hipGetLastError();
 }
 
