@@ -615,19 +615,27 @@ __device__ __forceinline__ void use_fstep(FState<T>& st, const D& d) {
     if constexpr (k < 2) {
       // QA = sum_e S(x+f,mu,e) S(x,f,e), QB = sum_e S(x+mu,f,e)^dagger S(x+f,mu,e); for
       // f = -a, S(.,f,e) is the dagger of the stored staple. Every factor is special
-      // unitary, so is every product: the first product of a sum is multiplied out as two
-      // rows and its third rebuilt (96 instructions); the second is accumulated in full
-      // (108; as two rows, rebuilt and added it would be 114) unless a factor would have
-      // to be rebuilt for it. Starting every sum from its first product instead of from
-      // zero and accumulating the second takes 324 of the 8,480 VALU instructions of a
-      // link: FP64 1.60 -> 1.57 ms a pass at 24^3 x 48, FP32 at 32^3 x 64 2.34 -> 2.33 ms.
+      // unitary, so is every product: two rows are multiplied out and the third rebuilt (96
+      // instructions). In FP64 the second product of a sum is accumulated in full instead
+      // (108; as two rows, rebuilt and added it is 114) unless a factor would have to be
+      // rebuilt for it; FP32 keeps its sums of rounded products (the fused action's W_C
+      // divides their rounding by c_C). Starting every sum from its first product instead of
+      // from zero and this accumulation: FP64 1.60 -> 1.57 ms a pass at 24^3 x 48.
       const su3<T> m = full(d.m);
-      if constexpr (k == 0) {
-        st.QA = full(rows_mul<(fs < 0)>(d.m, full(d.a)));
+      if constexpr (k == 0 || sizeof(T) == 4) {
+        const su3<T> qa = full(rows_mul<(fs < 0)>(d.m, full(d.a)));
+        su3<T> qb;
         if constexpr (fs > 0)
-          st.QB = full(rows_mul2<true, false>(full(d.b), m));
+          qb = full(rows_mul2<true, false>(full(d.b), m));
         else
-          st.QB = full(rows_mul<false>(d.b, m));
+          qb = full(rows_mul<false>(d.b, m));
+        if constexpr (k == 0) {
+          st.QA = qa;
+          st.QB = qb;
+        } else {
+          add(st.QA, qa);
+          add(st.QB, qb);
+        }
       } else {
         mac<false, (fs < 0)>(st.QA, m, full(d.a));
         if constexpr (fs > 0)
@@ -745,29 +753,6 @@ template <typename T>
 constexpr size_t small_lds_bytes() {
   return (size_t)kSmallSlots * 18 * 64 * sizeof(T);
 }
-
-template <typename T>
-struct LdsMats {
-  T* base;  // [slot][18][64]
-  int lane;
-
-  __device__ __forceinline__ void put(int slot, const su3<T>& m) const {
-#pragma unroll
-    for (int e = 0; e < 9; ++e) {
-      base[(slot * 18 + 2 * e) * 64 + lane] = m.e[e].re;
-      base[(slot * 18 + 2 * e + 1) * 64 + lane] = m.e[e].im;
-    }
-  }
-  __device__ __forceinline__ cx<T> elem_at(int slot, int e) const {
-    return cx<T>{base[(slot * 18 + 2 * e) * 64 + lane], base[(slot * 18 + 2 * e + 1) * 64 + lane]};
-  }
-  __device__ __forceinline__ su3<T> get(int slot) const {
-    su3<T> m;
-#pragma unroll
-    for (int e = 0; e < 9; ++e) m.e[e] = elem_at(slot, e);
-    return m;
-  }
-};
 
 template <typename T>
 struct Row {

@@ -10,6 +10,23 @@ using fat::Fields;
 
 namespace {
 
+// Tiles of the passes that read intermediate fields at neighbouring links: the walk of the
+// force pass (force_tile) with the parity fastest, so that the two parities of a chunk, which
+// read each other's fields, run side by side. These passes are bound by field data from
+// beyond the L2. FP32 at 32^3 x 64, against direction fastest in t-fastest slabs: FK2 2.65 ->
+// 2.56, FK3 1.44 -> 1.38, BK2 2.89 -> 2.88, GK 7.04 -> 6.73 ms (FK1, which reads links only, was
+// slower, 1.06 -> 1.12 ms, and keeps link_tile, as does BK3); 24^3 x 48, where the walk does not
+// apply and only the parity moves: 0.835 -> 0.810, 0.456 -> 0.451, 0.921 -> 0.908, 2.13 -> 2.11 ms.
+// FP64 at 32^4: FK2 2.23 -> 2.19, FK3 1.34 -> 1.26, BK2 2.62 -> 2.60 ms, but GK 6.40 -> 6.73 ms: the FP64
+// gather keeps link_tile.
+__device__ __forceinline__ LinkTile fat_tile(const Geom& g, int linear, int ntiles) {
+  LinkTile lt = force_tile(g, linear, ntiles, kBlock);
+  const int q = lt.p * 4 + lt.mu;
+  lt.p = q & 1;
+  lt.mu = q >> 1;
+  return lt;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void fat_fk1_kernel(Geom g, const T* __restrict__ U, Fields<T> w, FatCoeffs cf,
                                                           int ntiles) {
@@ -24,7 +41,7 @@ __global__ __launch_bounds__(kBlock) void fat_fk1_kernel(Geom g, const T* __rest
 template <typename T>
 __global__ __launch_bounds__(kBlock) void fat_fk2_kernel(Geom g, const T* __restrict__ U, Fields<T> w, FatCoeffs cf,
                                                           int ntiles) {
-  const LinkTile lt = link_tile(g, blockIdx.x, ntiles);
+  const LinkTile lt = fat_tile(g, blockIdx.x, ntiles);
   const int cb = lt.chunk * kBlock + threadIdx.x;
   if (cb >= g.Vh) return;
   Ctx<T> c;
@@ -50,11 +67,20 @@ __global__ __launch_bounds__(kBlock) void fat_fk2_kernel(Geom g, const T* __rest
   fat::store_m<3>(acc[2], c, w, T(cf.c[4]), cb);
 }
 
+// W = cN U_{x,mu} U_{x+mu,mu} U_{x+2mu,mu}
+template <typename T>
+__device__ __forceinline__ su3<T> naik_link(const Ctx<T>& c, const FatCoeffs& cf) {
+  su3<T> nk = mul<false, false>(c.template u<0, 0, 0, 0, 0>(), c.template u<1, 0, 0, 0, 0>());
+  nk = mul<false, false>(nk, c.template u<2, 0, 0, 0, 0>());
+  fat::scale(nk, T(cf.c[5]));
+  return nk;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void fat_fk3_kernel(Geom g, const T* __restrict__ U, Fields<T> w,
                                                           T* __restrict__ V, T* __restrict__ W, FatCoeffs cf,
                                                           int ntiles) {
-  const LinkTile lt = link_tile(g, blockIdx.x, ntiles);
+  const LinkTile lt = fat_tile(g, blockIdx.x, ntiles);
   const int cb = lt.chunk * kBlock + threadIdx.x;
   if (cb >= g.Vh) return;
   Ctx<T> c;
@@ -65,10 +91,7 @@ __global__ __launch_bounds__(kBlock) void fat_fk3_kernel(Geom g, const T* __rest
   store_link(block_ptr(V, lt.mu, lt.p, g.Vh), g.Vh, cb, acc);
   if (W != nullptr) {
     fat::launder(c);
-    su3<T> nk = mul<false, false>(c.template u<0, 0, 0, 0, 0>(), c.template u<1, 0, 0, 0, 0>());
-    nk = mul<false, false>(nk, c.template u<2, 0, 0, 0, 0>());
-    fat::scale(nk, T(cf.c[5]));
-    store_link(block_ptr(W, lt.mu, lt.p, g.Vh), g.Vh, cb, nk);
+    store_link(block_ptr(W, lt.mu, lt.p, g.Vh), g.Vh, cb, naik_link(c, cf));
   }
 }
 
@@ -87,7 +110,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
 template <typename T>
 __global__ __launch_bounds__(kBlock) void fat_bk2_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
                                                           Fields<T> w, FatCoeffs cf, int ntiles) {
-  const LinkTile lt = link_tile(g, blockIdx.x, ntiles);
+  const LinkTile lt = fat_tile(g, blockIdx.x, ntiles);
   const int cb = lt.chunk * kBlock + threadIdx.x;
   if (cb >= g.Vh) return;
   Ctx<T> c;
@@ -115,19 +138,10 @@ __global__ __launch_bounds__(kBlock) void fat_bk2_kernel(Geom g, const T* __rest
   fat::store_slot(w.D, 1, 0, lt.mu, lt.p, g.Vh, cb, dsum);
 }
 
-// Gradient (or force) of the thin link (y, nu): the direct terms D, the transports of
-// U_nu's own chain, the Naik terms, and the deposits of the transports along nu of the
-// other chains.
-template <typename T, int MODE>
-__global__ __launch_bounds__(kBlock) void fat_gk_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
-                                                         const T* __restrict__ GW, Fields<T> w, T* __restrict__ out,
-                                                         FatCoeffs cf, int ntiles) {
-  const LinkTile lt = link_tile(g, blockIdx.x, ntiles);
-  const int cb = lt.chunk * kBlock + threadIdx.x;
-  if (cb >= g.Vh) return;
-  Ctx<T> c;
-  fat::make_ctx(g, U, lt.mu, lt.p, cb, c);
-
+// The terms of a thin link's own chain: the direct terms D, the transports of U_nu itself,
+// and the Naik terms.
+template <typename T>
+__device__ __forceinline__ su3<T> own_terms(const Ctx<T>& c, const T* GW, const Fields<T>& w, const FatCoeffs& cf) {
   su3<T> acc = c.template f<0, 0, 0, 0, 0>(w.D, 1, 0);
   SYM_FAT_FENCE();
   fat::gk_pull<1>(acc, c, w);
@@ -147,21 +161,247 @@ __global__ __launch_bounds__(kBlock) void fat_gk_kernel(Geom g, const T* __restr
     axpy(acc, T(cf.c[5]), nk);
     SYM_FAT_FENCE();
   }
+  return acc;
+}
 
-  if constexpr (sizeof(T) == 4)
-    fat::gk_factor_pipe<1>(acc, c, GV, w);
-  else
-    fat::gk_factor_links_once<1>(acc, c, GV, w);
-
+// The gradient acc of link (mu, p, cb) to `out`, or the force of it.
+template <int MODE, typename T>
+__device__ __forceinline__ void store_result(const su3<T>& acc, const Ctx<T>& c0, T* out, int cb) {
+  Ctx<T> c = c0;
   fat::launder(c);
-  cx<T>* dst = block_ptr(out, lt.mu, lt.p, g.Vh);
+  cx<T>* dst = block_ptr(out, c.ax[0], c.p, c.Vh);
   if constexpr (MODE == 0) {
-    store_link(dst, g.Vh, cb, acc);
+    store_link(dst, c.Vh, cb, acc);
   } else {
     // G = -(1/2)(U grad^dagger)_TA, the force in the convention of the gauge force
     const su3<T> b = mul<false, true>(c.template u<0, 0, 0, 0, 0>(), acc);
-    store_link(dst, g.Vh, cb, ta_scaled(b, T(-0.5)));
+    store_link(dst, c.Vh, cb, ta_scaled(b, T(-0.5)));
   }
+}
+
+// Gradient (or force) of the thin link (y, nu): the terms of its own chain, and the deposits
+// of the transports along nu of the other chains.
+template <typename T, int MODE>
+__global__ __launch_bounds__(kBlock) void fat_gk_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
+                                                         const T* __restrict__ GW, Fields<T> w, T* __restrict__ out,
+                                                         FatCoeffs cf, int ntiles) {
+  const LinkTile lt = sizeof(T) == 4 ? fat_tile(g, blockIdx.x, ntiles) : link_tile(g, blockIdx.x, ntiles);
+  const int cb = lt.chunk * kBlock + threadIdx.x;
+  if (cb >= g.Vh) return;
+  Ctx<T> c;
+  fat::make_ctx(g, U, lt.mu, lt.p, cb, c);
+  su3<T> acc = own_terms(c, GW, w, cf);
+  fat::gk_chains<1>(acc, c, GV, w);
+  store_result<MODE>(acc, c, out, cb);
+}
+
+// ------------------------------------------------------------ small lattices
+// With one wave per 64 links small lattices leave most SIMDs empty and wait for one wave's
+// serial products. Here a workgroup of four waves shares 64 links (one per lane of every
+// wave), with partial sums in LDS. That pays up to two workgroups per CU (kFatSmallTiles).
+// Path force, before -> now: FP32 4^4 81 -> 42 us, 8^4 104 -> 47, 8^3 x 16 (512 workgroups) 107 -> 65;
+// FP64 4^4 90 -> 46 us, 8^4 124 -> 54, 8^3 x 16 136 -> 98. With 1024 workgroups (8^2 x 16^2) it would
+// be 117 -> 117 us in FP32 and 172 -> 194 us in FP64.
+
+// The link of a lane and its wave.
+template <typename T>
+struct SmallLink {
+  Ctx<T> c;
+  int cb, wave;
+  bool active;  // false past the end of the lattice: such lanes only take part in barriers
+};
+
+template <typename T>
+__device__ __forceinline__ SmallLink<T> small_link(const Geom& g, const T* U) {
+  SmallLink<T> s;
+  s.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  s.cb = (tile >> 3) * 64 + (threadIdx.x & 63);
+  s.active = s.cb < g.Vh;
+  s.cb = s.active ? s.cb : 0;
+  fat::make_ctx(g, U, tile & 3, (tile >> 2) & 1, s.cb, s.c);
+  return s;
+}
+
+// FK1 and BK3: wave K-1 writes slot K.
+template <typename T>
+__global__ __launch_bounds__(192) void fat_fk1_small_kernel(Geom g, const T* __restrict__ U, Fields<T> w, FatCoeffs cf) {
+  const SmallLink<T> s = small_link(g, U);
+  if (!s.active) return;
+  const T c5 = T(cf.c[2]), c7 = T(cf.c[3]);
+  if (s.wave == 0)
+    fat::fk1_one<1>(s.c, w, c5, c7, s.cb);
+  else if (s.wave == 1)
+    fat::fk1_one<2>(s.c, w, c5, c7, s.cb);
+  else
+    fat::fk1_one<3>(s.c, w, c5, c7, s.cb);
+}
+
+template <typename T>
+__global__ __launch_bounds__(192) void fat_bk3_small_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
+                                                            Fields<T> w) {
+  const SmallLink<T> s = small_link(g, U);
+  if (!s.active) return;
+  if (s.wave == 0)
+    fat::bk3_one<1>(s.c, GV, w, s.cb);
+  else if (s.wave == 1)
+    fat::bk3_one<2>(s.c, GV, w, s.cb);
+  else
+    fat::bk3_one<3>(s.c, GV, w, s.cb);
+}
+
+// FK2 and BK2, first half: wave J-1 forms the transports along ax[J], which serve the two
+// outputs other than J, into LDS slots 3 (J-1) + output.
+template <int J, bool BACK, typename T>
+__device__ __forceinline__ void small_two_out(const SmallLink<T>& s, const T* F, const LdsMats<T>& m) {
+  su3<T> acc[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) set_zero(acc[k]);
+  fat::two_out_one<J, BACK>(acc, s.c, F);
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    if (k != J - 1) m.put(3 * (J - 1) + k, acc[k]);
+}
+template <bool BACK, typename T>
+__device__ __forceinline__ void small_transports(const SmallLink<T>& s, const T* F, const LdsMats<T>& m) {
+  if (s.active) {
+    if (s.wave == 0)
+      small_two_out<1, BACK>(s, F, m);
+    else if (s.wave == 1)
+      small_two_out<2, BACK>(s, F, m);
+    else if (s.wave == 2)
+      small_two_out<3, BACK>(s, F, m);
+  }
+  __syncthreads();
+}
+// ... second half: the sum for output `k` in order of J.
+template <typename T>
+__device__ __forceinline__ void small_sum(su3<T>& acc, int k, const LdsMats<T>& m) {
+#pragma unroll
+  for (int j = 0; j < 3; ++j)
+    if (j != k) add(acc, m.get(3 * j + k));
+}
+
+template <int K, typename T>
+__device__ __forceinline__ void small_m(const SmallLink<T>& s, const Fields<T>& w, const FatCoeffs& cf,
+                                        const LdsMats<T>& m) {
+  su3<T> acc = s.c.template u<0, 0, 0, 0, 0>();
+  fat::scale(acc, T(cf.c[1]));
+  small_sum(acc, K - 1, m);
+  fat::store_m<K>(acc, s.c, w, T(cf.c[4]), s.cb);
+}
+
+template <typename T>
+__global__ __launch_bounds__(192) void fat_fk2_small_kernel(Geom g, const T* __restrict__ U, Fields<T> w, FatCoeffs cf) {
+  __shared__ T lds[9 * 18 * 64];
+  const SmallLink<T> s = small_link(g, U);
+  const LdsMats<T> m{lds, (int)(threadIdx.x & 63)};
+  small_transports<false>(s, static_cast<const T*>(w.inner), m);
+  if (!s.active) return;
+  if (s.wave == 0)
+    small_m<1>(s, w, cf, m);
+  else if (s.wave == 1)
+    small_m<2>(s, w, cf, m);
+  else
+    small_m<3>(s, w, cf, m);
+}
+
+template <int M, typename T>
+__device__ __forceinline__ void small_gt(const SmallLink<T>& s, const T* GV, const Fields<T>& w, const FatCoeffs& cf,
+                                         const LdsMats<T>& m) {
+  su3<T> gi;
+  set_zero(gi);
+  small_sum(gi, M - 1, m);
+  fat::store_gt<M>(gi, s.c, GV, w, T(cf.c[3]), T(cf.c[4]), s.cb);
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void fat_bk2_small_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
+                                                            Fields<T> w, FatCoeffs cf) {
+  __shared__ T lds[9 * 18 * 64];
+  const SmallLink<T> s = small_link(g, U);
+  const LdsMats<T> m{lds, (int)(threadIdx.x & 63)};
+  small_transports<true>(s, static_cast<const T*>(w.gmid), m);
+  if (!s.active) return;
+  if (s.wave == 0) {
+    small_gt<1>(s, GV, w, cf, m);
+  } else if (s.wave == 1) {
+    small_gt<2>(s, GV, w, cf, m);
+  } else if (s.wave == 2) {
+    small_gt<3>(s, GV, w, cf, m);
+  } else {
+    // D = c1 GV + c3 sum_k gmid_k + c5 sum_m g_inner_m
+    su3<T> d = s.c.template f<0, 0, 0, 0, 0>(GV, 1, 0);
+    fat::scale(d, T(cf.c[0]));
+    for (int k = 0; k < 3; ++k) axpy(d, T(cf.c[1]), s.c.template f<0, 0, 0, 0, 0>(w.gmid, 3, k));
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      su3<T> gi;
+      set_zero(gi);
+      small_sum(gi, k, m);
+      axpy(d, T(cf.c[2]), gi);
+    }
+    fat::store_slot(w.D, 1, 0, s.c.ax[0], s.c.p, g.Vh, s.cb, d);
+  }
+}
+
+// FK3: waves 0..2 the transports along ax[1..3], wave 3 the Naik link.
+template <typename T>
+__global__ __launch_bounds__(256) void fat_fk3_small_kernel(Geom g, const T* __restrict__ U, Fields<T> w,
+                                                            T* __restrict__ V, T* __restrict__ W, FatCoeffs cf) {
+  __shared__ T lds[2 * 18 * 64];
+  const SmallLink<T> s = small_link(g, U);
+  const LdsMats<T> m{lds, (int)(threadIdx.x & 63)};
+  su3<T> acc;
+  set_zero(acc);
+  if (s.active) {
+    if (s.wave == 0) {
+      acc = s.c.template u<0, 0, 0, 0, 0>();
+      fat::scale(acc, T(cf.c[0]));
+      fat::fk3_one<1>(acc, s.c, w);
+    } else if (s.wave == 1) {
+      fat::fk3_one<2>(acc, s.c, w);
+      m.put(0, acc);
+    } else if (s.wave == 2) {
+      fat::fk3_one<3>(acc, s.c, w);
+      m.put(1, acc);
+    } else if (W != nullptr) {
+      store_link(block_ptr(W, s.c.ax[0], s.c.p, g.Vh), g.Vh, s.cb, naik_link(s.c, cf));
+    }
+  }
+  __syncthreads();
+  if (!s.active || s.wave != 0) return;
+  add(acc, m.get(0));
+  add(acc, m.get(1));
+  store_link(block_ptr(V, s.c.ax[0], s.c.p, g.Vh), g.Vh, s.cb, acc);
+}
+
+// GK: wave 0 the own terms, waves 1..3 the deposits from the chains of ax[1..3].
+template <typename T, int MODE>
+__global__ __launch_bounds__(256) void fat_gk_small_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
+                                                           const T* __restrict__ GW, Fields<T> w, T* __restrict__ out,
+                                                           FatCoeffs cf) {
+  __shared__ T lds[3 * 18 * 64];
+  const SmallLink<T> s = small_link(g, U);
+  const LdsMats<T> m{lds, (int)(threadIdx.x & 63)};
+  su3<T> acc;
+  set_zero(acc);
+  if (s.active) {
+    if (s.wave == 0)
+      acc = own_terms(s.c, GW, w, cf);
+    else if (s.wave == 1)
+      fat::gk_chain<1>(acc, s.c, GV, w);
+    else if (s.wave == 2)
+      fat::gk_chain<2>(acc, s.c, GV, w);
+    else
+      fat::gk_chain<3>(acc, s.c, GV, w);
+    if (s.wave > 0) m.put(s.wave - 1, acc);
+  }
+  __syncthreads();
+  if (!s.active || s.wave != 0) return;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) add(acc, m.get(k));
+  store_result<MODE>(acc, s.c, out, s.cb);
 }
 
 }  // namespace
@@ -169,6 +409,10 @@ __global__ __launch_bounds__(kBlock) void fat_gk_kernel(Geom g, const T* __restr
 template <typename T>
 hipError_t launch_fat_fk3(const Geom& g, const T* U, T* V, T* W, const FatCoeffs& c, const Fields<T>& w,
                           hipStream_t s) {
+  if (fat_is_small(g)) {
+    fat_fk3_small_kernel<T><<<link_tiles(g, 64), 256, 0, s>>>(g, U, w, V, W, c);
+    return hipGetLastError();
+  }
   const int nt = link_tiles(g);
   fat_fk3_kernel<T><<<nt, kBlock, 0, s>>>(g, U, w, V, W, c, nt);
   return hipGetLastError();
@@ -177,6 +421,30 @@ hipError_t launch_fat_fk3(const Geom& g, const T* U, T* V, T* W, const FatCoeffs
 template <typename T>
 hipError_t launch_fat_stage(int stage, const Geom& g, const T* U, const T* GV, const T* GW, T* out, int mode,
                             const FatCoeffs& c, const Fields<T>& w, hipStream_t s) {
+  if (fat_is_small(g)) {
+    const int n = link_tiles(g, 64);
+    switch (stage) {
+      case 0:
+        fat_fk1_small_kernel<T><<<n, 192, 0, s>>>(g, U, w, c);
+        break;
+      case 1:
+        fat_fk2_small_kernel<T><<<n, 192, 0, s>>>(g, U, w, c);
+        break;
+      case 2:
+        fat_bk3_small_kernel<T><<<n, 192, 0, s>>>(g, U, GV, w);
+        break;
+      case 3:
+        fat_bk2_small_kernel<T><<<n, 256, 0, s>>>(g, U, GV, w, c);
+        break;
+      default:
+        if (mode == 0)
+          fat_gk_small_kernel<T, 0><<<n, 256, 0, s>>>(g, U, GV, GW, w, out, c);
+        else
+          fat_gk_small_kernel<T, 1><<<n, 256, 0, s>>>(g, U, GV, GW, w, out, c);
+        break;
+    }
+    return hipGetLastError();
+  }
   const int nt = link_tiles(g);
   switch (stage) {
     case 0:

@@ -269,24 +269,28 @@ __device__ __forceinline__ void scale(su3<T>& a, T s) {
 
 // FK1: inner[K-1] = c5 U + c7 (T1_{K,+} + T1_{K,-}) with T1_{K,s} = Sts_{ax[K]}(U_mu)
 template <int K, typename T>
-__device__ __forceinline__ void fk1_step(const Ctx<T>& c0, const Fields<T>& w, T c5, T c7, int cb) {
+__device__ __forceinline__ void fk1_one(const Ctx<T>& c0, const Fields<T>& w, T c5, T c7, int cb) {
+  Ctx<T> c = c0;
+  launder(c);
+  const auto A = u_only<T>();
+  su3<T> r;
+  set_zero(r);
+  st_acc<K, 1>(r, c, A);
+  su3<T> in = c.template u<0, 0, 0, 0, 0>();
+  scale(in, c5);
+  axpy(in, c7, r);
+  SYM_FAT_FENCE();
+  set_zero(r);
+  st_acc<K, -1>(r, c, A);
+  axpy(in, c7, r);
+  store_slot(w.inner, 3, K - 1, c.ax[0], c.p, c.Vh, cb, in);
+  SYM_FAT_FENCE();
+}
+template <int K, typename T>
+__device__ __forceinline__ void fk1_step(const Ctx<T>& c, const Fields<T>& w, T c5, T c7, int cb) {
   if constexpr (K <= 3) {
-    Ctx<T> c = c0;
-    launder(c);
-    const auto A = u_only<T>();
-    su3<T> r;
-    set_zero(r);
-    st_acc<K, 1>(r, c, A);
-    su3<T> in = c.template u<0, 0, 0, 0, 0>();
-    scale(in, c5);
-    axpy(in, c7, r);
-    SYM_FAT_FENCE();
-    set_zero(r);
-    st_acc<K, -1>(r, c, A);
-    axpy(in, c7, r);
-    store_slot(w.inner, 3, K - 1, c.ax[0], c.p, c.Vh, cb, in);
-    SYM_FAT_FENCE();
-    fk1_step<K + 1>(c0, w, c5, c7, cb);
+    fk1_one<K>(c, w, c5, c7, cb);
+    fk1_step<K + 1>(c, w, c5, c7, cb);
   }
 }
 
@@ -335,15 +339,19 @@ __device__ __forceinline__ void store_gt(const su3<T>& gi, const Ctx<T>& c0, con
 
 // FK3: V_mu = c1 U_mu + sum_{K,s} Sts_{ax[K]}(M[K, s])
 template <int K, typename T>
-__device__ __forceinline__ void fk3_step(su3<T>& acc, const Ctx<T>& c0, const Fields<T>& w) {
+__device__ __forceinline__ void fk3_one(su3<T>& acc, const Ctx<T>& c0, const Fields<T>& w) {
+  Ctx<T> c = c0;
+  launder(c);
+  st_acc<K, 1>(acc, c, one(static_cast<const T*>(w.M), 6, 2 * (K - 1)));
+  SYM_FAT_FENCE();
+  st_acc<K, -1>(acc, c, one(static_cast<const T*>(w.M), 6, 2 * (K - 1) + 1));
+  SYM_FAT_FENCE();
+}
+template <int K, typename T>
+__device__ __forceinline__ void fk3_step(su3<T>& acc, const Ctx<T>& c, const Fields<T>& w) {
   if constexpr (K <= 3) {
-    Ctx<T> c = c0;
-    launder(c);
-    st_acc<K, 1>(acc, c, one(static_cast<const T*>(w.M), 6, 2 * (K - 1)));
-    SYM_FAT_FENCE();
-    st_acc<K, -1>(acc, c, one(static_cast<const T*>(w.M), 6, 2 * (K - 1) + 1));
-    SYM_FAT_FENCE();
-    fk3_step<K + 1>(acc, c0, w);
+    fk3_one<K>(acc, c, w);
+    fk3_step<K + 1>(acc, c, w);
   }
 }
 
@@ -351,22 +359,26 @@ __device__ __forceinline__ void fk3_step(su3<T>& acc, const Ctx<T>& c0, const Fi
 
 // BK3: gmid[K-1] = gM[K, +] + gM[K, -] with gM[K, S] = St-S_{ax[K]}(GV_mu)
 template <int K, typename T>
-__device__ __forceinline__ void bk3_step(const Ctx<T>& c0, const T* GV, const Fields<T>& w, int cb) {
+__device__ __forceinline__ void bk3_one(const Ctx<T>& c0, const T* GV, const Fields<T>& w, int cb) {
+  Ctx<T> c = c0;
+  launder(c);
+  const auto G = one(GV, 1, 0);
+  su3<T> r, gm;
+  set_zero(r);
+  st_acc<K, -1>(r, c, G);
+  gm = r;
+  SYM_FAT_FENCE();
+  set_zero(r);
+  st_acc<K, 1>(r, c, G);
+  add(gm, r);
+  store_slot(w.gmid, 3, K - 1, c.ax[0], c.p, c.Vh, cb, gm);
+  SYM_FAT_FENCE();
+}
+template <int K, typename T>
+__device__ __forceinline__ void bk3_step(const Ctx<T>& c, const T* GV, const Fields<T>& w, int cb) {
   if constexpr (K <= 3) {
-    Ctx<T> c = c0;
-    launder(c);
-    const auto G = one(GV, 1, 0);
-    su3<T> r, gm;
-    set_zero(r);
-    st_acc<K, -1>(r, c, G);
-    gm = r;
-    SYM_FAT_FENCE();
-    set_zero(r);
-    st_acc<K, 1>(r, c, G);
-    add(gm, r);
-    store_slot(w.gmid, 3, K - 1, c.ax[0], c.p, c.Vh, cb, gm);
-    SYM_FAT_FENCE();
-    bk3_step<K + 1>(c0, GV, w, cb);
+    bk3_one<K>(c, GV, w, cb);
+    bk3_step<K + 1>(c, GV, w, cb);
   }
 }
 
@@ -401,18 +413,22 @@ __device__ __forceinline__ void two_out_step(su3<T> (&acc)[3], const Ctx<T>& c, 
 }
 
 template <int J, bool BACK, typename T>
-__device__ __forceinline__ void two_out(su3<T> (&acc)[3], const Ctx<T>& c0, const T* F) {
+__device__ __forceinline__ void two_out_one(su3<T> (&acc)[3], const Ctx<T>& c0, const T* F) {
+  constexpr int e1 = comp(1, J), e2 = comp(2, J), e3 = comp(3, J);
+  Ctx<T> c = c0;
+  launder(c);
+  asm volatile("" : "+s"(F));
+  const su3<T> u0 = c.template u<0, 0, 0, 0, J>();              // U_{x,J}
+  const su3<T> u1 = c.template u<1, 0, 0, 0, J>();              // U_{x+mu,J}
+  const su3<T> v0 = c.template u<0, -e1, -e2, -e3, J>();        // U_{x-J,J}
+  const su3<T> v1 = c.template u<1, -e1, -e2, -e3, J>();        // U_{x-J+mu,J}
+  two_out_step<J, 1, BACK>(acc, c, F, u0, u1, v0, v1);
+}
+template <int J, bool BACK, typename T>
+__device__ __forceinline__ void two_out(su3<T> (&acc)[3], const Ctx<T>& c, const T* F) {
   if constexpr (J <= 3) {
-    constexpr int e1 = comp(1, J), e2 = comp(2, J), e3 = comp(3, J);
-    Ctx<T> c = c0;
-    launder(c);
-    asm volatile("" : "+s"(F));
-    const su3<T> u0 = c.template u<0, 0, 0, 0, J>();              // U_{x,J}
-    const su3<T> u1 = c.template u<1, 0, 0, 0, J>();              // U_{x+mu,J}
-    const su3<T> v0 = c.template u<0, -e1, -e2, -e3, J>();        // U_{x-J,J}
-    const su3<T> v1 = c.template u<1, -e1, -e2, -e3, J>();        // U_{x-J+mu,J}
-    two_out_step<J, 1, BACK>(acc, c, F, u0, u1, v0, v1);
-    two_out<J + 1, BACK>(acc, c0, F);
+    two_out_one<J, BACK>(acc, c, F);
+    two_out<J + 1, BACK>(acc, c, F);
   }
 }
 
@@ -540,38 +556,32 @@ __device__ __forceinline__ void dep_serial(su3<T>& acc, const Ctx<T>& c, const T
   }
 }
 
-// The same deposits without the look-ahead (FP64: no registers for two transports).
+// The deposits from the chains of mu = ax[I], the two links loaded once. FP32 requests the
+// next transport's matrices ahead; FP64 has no registers for two transports.
 template <int I, typename T>
-__device__ __forceinline__ void gk_factor_links_once(su3<T>& acc, const Ctx<T>& c0, const T* GV,
-                                                     const Fields<T>& w) {
-  if constexpr (I <= 3) {
-    constexpr int e1 = comp(1, I), e2 = comp(2, I), e3 = comp(3, I);
-    const int mu = c0.ax[I], nu = c0.ax[0];
-    const int kn = nu < mu ? nu : nu - 1;
-    Ctx<T> c = c0;
-    launder(c);
-    const su3<T> up = c.template u<0, e1, e2, e3, 0>();
-    const su3<T> um = c.template u<0, -e1, -e2, -e3, 0>();
+__device__ __forceinline__ void gk_chain(su3<T>& acc, const Ctx<T>& c0, const T* GV, const Fields<T>& w) {
+  constexpr int e1 = comp(1, I), e2 = comp(2, I), e3 = comp(3, I);
+  const int mu = c0.ax[I], nu = c0.ax[0];
+  const int kn = nu < mu ? nu : nu - 1;
+  Ctx<T> c = c0;
+  launder(c);
+  const su3<T> up = c.template u<0, e1, e2, e3, 0>();     // U_{y+mu,nu}
+  const su3<T> um = c.template u<0, -e1, -e2, -e3, 0>();  // U_{y-mu,nu}
+  if constexpr (sizeof(T) == 4) {
+    const Dep<T> d0 = load_dep<I, 0>(c, GV, w, kn);
+    SYM_FAT_FENCE();
+    dep_pipe<I, 0>(acc, c, GV, w, kn, up, um, d0);
+  } else {
     SYM_FAT_FENCE();
     dep_serial<I, 0>(acc, c, GV, w, kn, up, um);
-    gk_factor_links_once<I + 1>(acc, c0, GV, w);
   }
 }
 
 template <int I, typename T>
-__device__ __forceinline__ void gk_factor_pipe(su3<T>& acc, const Ctx<T>& c0, const T* GV, const Fields<T>& w) {
+__device__ __forceinline__ void gk_chains(su3<T>& acc, const Ctx<T>& c, const T* GV, const Fields<T>& w) {
   if constexpr (I <= 3) {
-    constexpr int e1 = comp(1, I), e2 = comp(2, I), e3 = comp(3, I);
-    const int mu = c0.ax[I], nu = c0.ax[0];
-    const int kn = nu < mu ? nu : nu - 1;
-    Ctx<T> c = c0;
-    launder(c);
-    const su3<T> up = c.template u<0, e1, e2, e3, 0>();     // U_{y+mu,nu}
-    const su3<T> um = c.template u<0, -e1, -e2, -e3, 0>();  // U_{y-mu,nu}
-    const Dep<T> d0 = load_dep<I, 0>(c, GV, w, kn);
-    SYM_FAT_FENCE();
-    dep_pipe<I, 0>(acc, c, GV, w, kn, up, um, d0);
-    gk_factor_pipe<I + 1>(acc, c0, GV, w);
+    gk_chain<I>(acc, c, GV, w);
+    gk_chains<I + 1>(acc, c, GV, w);
   }
 }
 
@@ -579,6 +589,11 @@ __device__ __forceinline__ void gk_factor_pipe(su3<T>& acc, const Ctx<T>& c0, co
 }  // namespace sym
 
 namespace sym {
+
+// On lattices with at most kFatSmallTiles workgroups of 64 links the passes share the links
+// of a workgroup between its waves (small-lattice kernels in fat.hip).
+constexpr int kFatSmallTiles = 2 * kCUs;
+inline bool fat_is_small(const Geom& g) { return link_tiles(g, 64) <= kFatSmallTiles; }
 
 // Last pass of the fat links: V and Naik links W (W may be null) from T1 and midc
 // (stages 0 and 1 below).

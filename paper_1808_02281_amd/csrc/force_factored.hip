@@ -47,8 +47,8 @@ __global__ __launch_bounds__(64 * factored::kSmallWaves) void force_small_kernel
                                                                                  Coeffs cf) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const factored::LdsMats<T> m{reinterpret_cast<T*>(lds), (int)(threadIdx.x & 63)};
-  const int tile = blockIdx.x;
+  const LdsMats<T> m{reinterpret_cast<T*>(lds), (int)(threadIdx.x & 63)};
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int cb = (tile >> 3) * 64 + m.lane;
   const bool active = cb < g.Vh;
   double a[3] = {0.0, 0.0, 0.0};

@@ -291,6 +291,31 @@ __device__ __forceinline__ SiteTile site_tile(const Geom& g, int linear, int nti
   return r;
 }
 
+// Matrices exchanged between the waves of a workgroup that share 64 sites or links, one
+// per lane: [slot][18][64] reals in LDS.
+template <typename T>
+struct LdsMats {
+  T* base;
+  int lane;
+
+  __device__ __forceinline__ void put(int slot, const su3<T>& m) const {
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      base[(slot * 18 + 2 * e) * 64 + lane] = m.e[e].re;
+      base[(slot * 18 + 2 * e + 1) * 64 + lane] = m.e[e].im;
+    }
+  }
+  __device__ __forceinline__ cx<T> elem_at(int slot, int e) const {
+    return cx<T>{base[(slot * 18 + 2 * e) * 64 + lane], base[(slot * 18 + 2 * e + 1) * 64 + lane]};
+  }
+  __device__ __forceinline__ su3<T> get(int slot) const {
+    su3<T> m;
+#pragma unroll
+    for (int e = 0; e < 9; ++e) m.e[e] = elem_at(slot, e);
+    return m;
+  }
+};
+
 // ------------------------------------------------------------ FP64 reductions
 // Fixed-order (deterministic) sums: wavefront butterfly, then the block's waves in
 // order. No atomics.
