@@ -3,9 +3,23 @@
 // leapfrog Hamiltonian.
 //
 // Action kernel: w_X = sum over sites and class-X loops of (3 - Re tr P), in double, with
-// the 34 loops of a site (eq. 18_6_6_3_0) closed from halves that meet in a trace. No
-// unitarity is assumed, so the links are read in full. With the two ways around the
-// (nu, rho) square of a site, P = U_{y,nu} U_{y+nu,rho} and Q = U_{y,rho} U_{y+rho,nu}:
+// the 34 loops of a site (eq. 18_6_6_3_0), the last product of each replaced by its trace.
+// No unitarity is assumed, so the links are read in full.
+//
+// A workgroup is 64 sites whose four waves share the loops. With one thread per site, what
+// bounded the kernel was link data from beyond the L2 (16 GB for 0.4 GB of links at 24^3 x 48
+// in FP64, 7.1 TB/s). 64 sites per workgroup instead of 256 keep the links of the sites in
+// flight on an XCD within its 4 MiB of L2 (1.5 GB fetched), in the t-fastest slab order of the
+// other passes, and small lattices get four times the waves with a quarter of the serial work
+// each. The axes are wave-uniform values rather than template arguments, so the four waves
+// share one code. The bound now is the vector load path (TD busy 0.94 in FP64, VALU 0.44).
+//
+// FP32 multiplies every loop out from its base site link by link (loops that start with the
+// same two links share that product): the double sums carry the float rounding of every
+// trace, and this way an FP32 action does not depend on how the loops are shared. FP64
+// closes the loops from halves that meet in a trace, fewer loads for the same products. With the
+// two ways around the (nu, rho) square of a site, P = U_{y,nu} U_{y+nu,rho} and
+// Q = U_{y,rho} U_{y+rho,nu}:
 //   plaquette   tr(P Q^+);
 //   rectangles  tr((U_{y,nu} P_{y+nu}) (Q_y U_{y+nu+rho,nu})^+) and the same with nu and
 //               rho exchanged;
@@ -14,28 +28,19 @@
 //               loop with nu and rho both reversed, and the two loops with one of them
 //               reversed have the same form with the square's other two sides
 //               E = U_{y+rho,nu} U_{y+nu,rho}^+ and F = U_{y,rho}^+ U_{y,nu}.
-// Every loop is summed once over the lattice (its base site differs from the paper's by a
-// translation). Four (square, mu) pairs cover the four axis triples.
+// Every loop is summed once over the lattice (its base site differs by a translation). Four
+// (square, mu) pairs cover the four axis triples.
 //
-// A workgroup is 64 sites, its four waves share the loops: wave k takes the cube loops of
-// one (square, mu) pair and one or two squares' plaquette and rectangles. With one thread
-// per site multiplying out all 34 loops, what bounded the kernel was link data from beyond
-// the L2 (16 GB for 0.4 GB of links at 24^3 x 48 in FP64, 7.1 TB/s). 64 sites per workgroup
-// instead of 256 keep the links of the sites in flight on an XCD within its 4 MiB of L2
-// (1.5 GB fetched), in the t-fastest slab order of the force passes, and small lattices
-// get four times the waves with a quarter of the serial work each. The squares' axes are
-// wave-uniform values rather than template arguments, so the four waves share one code.
-// Measured, before -> now: FP64 24^3 x 48 2.25 -> 0.61 ms, FP32 32^3 x 64 3.37 -> 1.08 ms,
-// FP64 4^4 107 -> 17 us. The bound now is the vector load path (TD busy 0.94 in FP64, VALU
-// 0.44).
+// Measured, before -> now: FP64 24^3 x 48 2.25 -> 0.61 ms (0.74 ms with the FP32 form), 4^4
+// 107 -> 17 us; FP32 32^3 x 64 3.37 -> 1.38 ms (halves: 1.08 to 1.21 ms).
 #include "kernels.hpp"
 
 namespace sym {
 namespace {
 
-// Lexicographic index steps of one and two links forwards along an axis.
+// Lexicographic index steps of one and two links forwards and one backwards along an axis.
 struct Step {
-  int one, two;
+  int one, two, back;
 };
 
 template <typename T>
@@ -51,12 +56,12 @@ struct LoopSite {
   }
 };
 
-// Fence between groups of loops: links that several groups read are loaded again (they hit
-// L1) rather than kept in registers, no load moves ahead of its group, and the group's sum
-// is finished where it stands (the compiler otherwise sinks the products to the use of w
-// and keeps every link alive until there).
+// Fence between loops: links that several loops read are loaded again (they hit L1) rather
+// than kept in registers, no load moves ahead of its loop, and the loop's sum is finished
+// where it stands (the compiler otherwise sinks the products to the use of w and keeps
+// every link alive until there).
 template <typename T>
-__device__ __forceinline__ LoopSite<T> next_group(const LoopSite<T>& s, double& w) {
+__device__ __forceinline__ LoopSite<T> next_loop(const LoopSite<T>& s, double& w) {
   LoopSite<T> r = s;
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("" : "+s"(r.U), "+v"(w));
@@ -70,90 +75,101 @@ __device__ __forceinline__ Step step_along(const Geom& g, const int x[4], int a)
   Step s;
   s.one = (xa + 1 < La ? 1 : 1 - La) * stride;
   s.two = (xa + 2 < La ? 2 : 2 - La) * stride;
+  s.back = (xa > 0 ? -1 : La - 1) * stride;
   return s;
 }
+
+// ----------------------------------------------------------- loop by loop (FP32)
+
+// (m, n, -m, -n)
+template <typename T>
+__device__ __forceinline__ void plaquette(const LoopSite<T>& s0, int m, int n, Step dm, Step dn, double& w) {
+  const LoopSite<T> s = next_loop(s0, w);
+  su3<T> p = mul<false, false>(s.link(m, 0, 0), s.link(n, 1, dm.one));
+  p = mul<false, true>(p, s.link(m, 1, dn.one));
+  w += 3.0 - re_tr_mul<true>(p, s.link(n, 0, 0));
+}
+
+// (m, m, n, -m, -m, -n), mm = U_{x,m} U_{x+m,m}
+template <typename T>
+__device__ __forceinline__ void rectangle(const LoopSite<T>& s0, const su3<T>& mm, int m, int n, Step dm, Step dn,
+                                          double& w) {
+  const LoopSite<T> s = next_loop(s0, w);
+  su3<T> p = mul<false, false>(mm, s.link(n, 0, dm.two));
+  p = mul<false, true>(p, s.link(m, 0, dm.one + dn.one));
+  p = mul<false, true>(p, s.link(m, 1, dn.one));
+  w += 3.0 - re_tr_mul<true>(p, s.link(n, 0, 0));
+}
+
+// (m, SN n, SR r, -m, -SN n, -SR r), mn = U_{x,m} U_{x+m,SN n}
+template <int SN, int SR, typename T>
+__device__ __forceinline__ void cube_loop(const LoopSite<T>& s0, const su3<T>& mn, int m, int n, int r, Step dm,
+                                          Step dn, Step dr, double& w) {
+  const LoopSite<T> s = next_loop(s0, w);
+  const int on = SN > 0 ? dn.one : dn.back, orr = SR > 0 ? dr.one : dr.back;
+  su3<T> p;
+  if constexpr (SR > 0)
+    p = mul<false, false>(mn, s.link(r, 0, dm.one + on));
+  else
+    p = mul<false, true>(mn, s.link(r, 1, dm.one + on + dr.back));
+  p = mul<false, true>(p, s.link(m, 0, on + orr));
+  if constexpr (SN > 0)
+    p = mul<false, true>(p, s.link(n, 1, orr));
+  else
+    p = mul<false, false>(p, s.link(n, 0, dn.back + orr));
+  if constexpr (SR > 0)
+    w += 3.0 - re_tr_mul<true>(p, s.link(r, 0, 0));
+  else
+    w += 3.0 - re_tr_mul<false>(p, s.link(r, 1, dr.back));
+}
+
+template <int SN, typename T>
+__device__ __forceinline__ void cube_pair(const LoopSite<T>& s0, int m, int n, int r, Step dm, Step dn, Step dr,
+                                          double& w) {
+  const LoopSite<T> s = next_loop(s0, w);
+  su3<T> mn;
+  if constexpr (SN > 0)
+    mn = mul<false, false>(s.link(m, 0, 0), s.link(n, 1, dm.one));
+  else
+    mn = mul<false, true>(s.link(m, 0, 0), s.link(n, 0, dm.one + dn.back));
+  cube_loop<SN, 1>(s, mn, m, n, r, dm, dn, dr, w);
+  cube_loop<SN, -1>(s, mn, m, n, r, dm, dn, dr, w);
+}
+
+// ------------------------------------------------------------------ halves (FP64)
 
 // Plaquette and both rectangles of the (nu, rho) square: 8 products, 3 traces.
 template <typename T>
 __device__ __forceinline__ void square_loops(const LoopSite<T>& s0, int nu, int rho, Step dn, Step dr, double w[3]) {
-  const LoopSite<T> s1 = next_group(s0, w[1]);
+  const LoopSite<T> s1 = next_loop(s0, w[1]);
   const su3<T> un = s1.link(nu, 0, 0), ur = s1.link(rho, 0, 0);
   const su3<T> P = mul<false, false>(un, s1.link(rho, 1, dn.one));
   const su3<T> Q = mul<false, false>(ur, s1.link(nu, 1, dr.one));
   w[0] += 3.0 - re_tr_mul<true>(P, Q);
   {  // long side along nu
-    const LoopSite<T> s = next_group(s1, w[0]);
+    const LoopSite<T> s = next_loop(s1, w[0]);
     const su3<T> a = mul<false, false>(un, mul<false, false>(s.link(nu, 1, dn.one), s.link(rho, 0, dn.two)));
     const su3<T> b = mul<false, false>(Q, s.link(nu, 0, dn.one + dr.one));
     w[1] += 3.0 - re_tr_mul<true>(a, b);
   }
   {  // long side along rho
-    const LoopSite<T> s = next_group(s1, w[1]);
+    const LoopSite<T> s = next_loop(s1, w[1]);
     const su3<T> a = mul<false, false>(ur, mul<false, false>(s.link(rho, 1, dr.one), s.link(nu, 0, dr.two)));
     const su3<T> b = mul<false, false>(P, s.link(rho, 0, dn.one + dr.one));
     w[1] += 3.0 - re_tr_mul<true>(a, b);
   }
-  (void)next_group(s1, w[1]);
+  (void)next_loop(s1, w[1]);
 }
 
-// The four cube loops of the (nu, rho) square carried along mu: 16 products, 4 traces. Two
-// orders of the same products. cube_loops_ring (FP32) finishes the square's four sides at
-// y first and then walks the square at y+mu corner by corner, each of its links serving
-// the two sides it lies on: 14 link loads. It holds six matrices and more, which in FP64
-// is 298 registers (one wave per SIMD) or spills; cube_loops_diag (FP64) takes the square's
-// two diagonals in turn, with 20 link loads, at two waves per SIMD. FP32, 32^3 x 64:
-// ring 1.08 ms, diag 1.21 ms; FP64, 24^3 x 48: ring 0.70 ms (one wave) or 0.80 ms (two
-// waves, 54 spilled registers), diag 0.61 ms.
+// The four cube loops of the (nu, rho) square carried along mu: 16 products, 4 traces, the
+// two diagonals of the square in turn (two waves per SIMD; the square's four sides at once
+// would load 14 links instead of 20 but take 298 registers: 0.70 ms at one wave, 0.80 ms with
+// spills at two, against 0.61).
 template <typename T>
-__device__ __forceinline__ void cube_loops_ring(const LoopSite<T>& s0, int nu, int rho, int mu, Step dn, Step dr, Step dm,
-                                                double w[3]) {
-  const LoopSite<T> s = next_group(s0, w[2]);
-  su3<T> P, Q, E, F;
+__device__ __forceinline__ void cube_loops(const LoopSite<T>& s0, int nu, int rho, int mu, Step dn, Step dr, Step dm,
+                                           double w[3]) {
   {
-    const su3<T> a = s.link(nu, 0, 0), b = s.link(rho, 1, dn.one);
-    const su3<T> c = s.link(rho, 0, 0), d = s.link(nu, 1, dr.one);
-    const su3<T> um = s.link(mu, 0, dn.one + dr.one);
-    P = mul<false, false>(mul<false, false>(a, b), um);
-    Q = mul<false, false>(mul<false, false>(c, d), um);
-    const su3<T> un = s.link(mu, 1, dn.one);
-    E = mul<false, false>(mul<false, true>(d, b), un);
-    F = mul<false, false>(mul<true, false>(c, a), un);
-  }
-  const LoopSite<T> t = next_group(s, w[2]);
-  const su3<T> b1 = t.link(rho, 0, dn.one + dm.one);
-  {
-    const su3<T> u0 = t.link(mu, 0, 0);
-    const su3<T> P1 = mul<false, false>(t.link(nu, 1, dm.one), b1);
-    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u0, P1), Q);
-  }
-  LoopSite<T> v = next_group(t, w[2]);
-  const su3<T> d1 = v.link(nu, 0, dr.one + dm.one);
-  {
-    const su3<T> u1 = v.link(mu, 1, dr.one);
-    const su3<T> E1 = mul<false, true>(d1, b1);
-    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u1, E1), F);
-  }
-  v = next_group(v, w[2]);
-  const su3<T> c1 = v.link(rho, 1, dm.one);
-  {
-    const su3<T> u0 = v.link(mu, 0, 0);
-    const su3<T> Q1 = mul<false, false>(c1, d1);
-    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u0, Q1), P);
-  }
-  v = next_group(v, w[2]);
-  {
-    const su3<T> u1 = v.link(mu, 1, dr.one);
-    const su3<T> F1 = mul<true, false>(c1, v.link(nu, 1, dm.one));
-    w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u1, F1), E);
-  }
-  (void)next_group(s0, w[2]);
-}
-
-template <typename T>
-__device__ __forceinline__ void cube_loops_diag(const LoopSite<T>& s0, int nu, int rho, int mu, Step dn, Step dr, Step dm,
-                                                double w[3]) {
-  {
-    const LoopSite<T> s = next_group(s0, w[2]);
+    const LoopSite<T> s = next_loop(s0, w[2]);
     const su3<T> um = s.link(mu, 0, dn.one + dr.one);
     const su3<T> P = mul<false, false>(mul<false, false>(s.link(nu, 0, 0), s.link(rho, 1, dn.one)), um);
     const su3<T> Q = mul<false, false>(mul<false, false>(s.link(rho, 0, 0), s.link(nu, 1, dr.one)), um);
@@ -166,7 +182,7 @@ __device__ __forceinline__ void cube_loops_diag(const LoopSite<T>& s0, int nu, i
     w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u0, Q1), P);
   }
   {
-    const LoopSite<T> s = next_group(s0, w[2]);
+    const LoopSite<T> s = next_loop(s0, w[2]);
     const su3<T> um = s.link(mu, 1, dn.one);
     const su3<T> E = mul<false, false>(mul<false, true>(s.link(nu, 1, dr.one), s.link(rho, 1, dn.one)), um);
     const su3<T> F = mul<false, false>(mul<true, false>(s.link(rho, 0, 0), s.link(nu, 0, 0)), um);
@@ -178,16 +194,7 @@ __device__ __forceinline__ void cube_loops_diag(const LoopSite<T>& s0, int nu, i
     const su3<T> F1 = mul<true, false>(s.link(rho, 1, dm.one), s.link(nu, 1, dm.one));
     w[2] += 3.0 - re_tr_mul<true>(mul<false, false>(u1, F1), E);
   }
-  (void)next_group(s0, w[2]);
-}
-
-template <typename T>
-__device__ __forceinline__ void cube_loops(const LoopSite<T>& s, int nu, int rho, int mu, Step dn, Step dr, Step dm,
-                                           double w[3]) {
-  if constexpr (sizeof(T) == 4)
-    cube_loops_ring(s, nu, rho, mu, dn, dr, dm, w);
-  else
-    cube_loops_diag(s, nu, rho, mu, dn, dr, dm, w);
+  (void)next_loop(s0, w[2]);
 }
 
 constexpr int kActionSites = 64;  // sites per workgroup, one per lane of each of its waves
@@ -206,18 +213,41 @@ __global__ __launch_bounds__(kBlock) void action_kernel(Geom g, const T* __restr
     s.Vh = g.Vh;
     s.p = st.p;
     s.lex = 2 * cb + (x[0] & 1);
-    // the waves' shares rotate with the workgroup, so that the two longer ones do not
-    // always land on the same SIMDs
+    // the waves' shares rotate with the workgroup, so that the longer ones do not always land
+    // on the same SIMDs
     const int k = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + (int)blockIdx.x) & 3;
-    // cube loops: squares 01, 01, 02, 12 carried along 2, 3, 3, 3
-    const int nu = k == 3 ? 1 : 0, rho = k < 2 ? 1 : 2, mu = k == 0 ? 2 : 3;
-    cube_loops(s, nu, rho, mu, step_along(g, x, nu), step_along(g, x, rho), step_along(g, x, mu), w);
-    // plaquettes and rectangles: squares 01, 23 | 02, 13 | 03 | 12
-    const int n1 = k == 3 ? 1 : 0, r1 = k == 0 ? 1 : k == 2 ? 3 : 2;
-    square_loops(s, n1, r1, step_along(g, x, n1), step_along(g, x, r1), w);
-    if (k < 2) {
-      const int n2 = k == 0 ? 2 : 1;
-      square_loops(s, n2, 3, step_along(g, x, n2), step_along(g, x, 3), w);
+    if constexpr (sizeof(T) == 4) {
+      {  // cube loops of the triples 012, 013, 023, 123
+        const int m = k == 3 ? 1 : 0, n = k < 2 ? 1 : 2, r = k == 0 ? 2 : 3;
+        const Step dm = step_along(g, x, m), dn = step_along(g, x, n), dr = step_along(g, x, r);
+        cube_pair<1>(s, m, n, r, dm, dn, dr, w[2]);
+        cube_pair<-1>(s, m, n, r, dm, dn, dr, w[2]);
+      }
+      const Step dk = step_along(g, x, k);
+      {  // rectangles with the long side along k
+        const LoopSite<T> t = next_loop(s, w[2]);
+        const su3<T> kk = mul<false, false>(t.link(k, 0, 0), t.link(k, 1, dk.one));
+        const int a = k == 0 ? 1 : 0, b = k <= 1 ? 2 : 1, c = k <= 2 ? 3 : 2;
+        rectangle(t, kk, k, a, dk, step_along(g, x, a), w[1]);
+        rectangle(t, kk, k, b, dk, step_along(g, x, b), w[1]);
+        rectangle(t, kk, k, c, dk, step_along(g, x, c), w[1]);
+      }
+      // plaquettes 01 03 | 12 13 | 23 | 02
+      if (k < 3) plaquette(s, k, k + 1, dk, step_along(g, x, k + 1), w[0]);
+      if (k < 2) plaquette(s, k, 3, dk, step_along(g, x, 3), w[0]);
+      if (k == 3) plaquette(s, 0, 2, step_along(g, x, 0), step_along(g, x, 2), w[0]);
+      (void)next_loop(s, w[0]);
+    } else {
+      // cube loops: squares 01, 01, 02, 12 carried along 2, 3, 3, 3
+      const int nu = k == 3 ? 1 : 0, rho = k < 2 ? 1 : 2, mu = k == 0 ? 2 : 3;
+      cube_loops(s, nu, rho, mu, step_along(g, x, nu), step_along(g, x, rho), step_along(g, x, mu), w);
+      // plaquettes and rectangles: squares 01, 23 | 02, 13 | 03 | 12
+      const int n1 = k == 3 ? 1 : 0, r1 = k == 0 ? 1 : k == 2 ? 3 : 2;
+      square_loops(s, n1, r1, step_along(g, x, n1), step_along(g, x, r1), w);
+      if (k < 2) {
+        const int n2 = k == 0 ? 2 : 1;
+        square_loops(s, n2, 3, step_along(g, x, n2), step_along(g, x, 3), w);
+      }
     }
   }
   block_sum_store<3>(w, partials + 3 * (size_t)blockIdx.x);

@@ -237,9 +237,9 @@ __device__ __forceinline__ LinkTile link_tile(const Geom& g, int linear, int nti
 // (times 8 directions and parities) are in flight on an XCD, and the walk is z in fours
 // fastest, then t through the XCD's slab of ceil(Lt/8) slices, then the blocks of four z,
 // then y. At 32^3 x 64, against t fastest over the slab and then y and z (link_tile):
-// FP32 2.33 -> 2.11 ms, FP64 4.95 -> 4.34 ms. That needs chunks that lie in one (x, y) plane;
+// FP32 2.33 -> 2.15 ms, FP64 4.95 -> 4.22 ms. That needs chunks that lie in one (x, y) plane;
 // where a plane is not whole chunks the z-neighbours of a chunk straddle two others, and
-// the same walk over rounded plane sizes was slower (24^3 x 48: FP64 1.51 -> 1.89 ms, FP32
+// the same walk over rounded plane sizes was slower (24^3 x 48: FP64 1.57 -> 1.89 ms, FP32
 // 0.70 -> 0.71 ms): such lattices keep link_tile.
 __device__ __forceinline__ bool planes_are_chunks(const Geom& g, int n) { return g.Lxh * g.L[1] % n == 0; }
 
