@@ -325,6 +325,38 @@ __device__ __forceinline__ su3<T> dagger(const su3<T>& a) {
   return r;
 }
 
+// Products with an insertion K, whose diagonal is imaginary: its zero real parts are left out
+// (the compiler keeps a multiplication by a constant zero), 90 instructions against 108.
+//   add_k<false, D>: C += K M^{D};  add_k<true, D>: C += M^{D} K;  with SET, C is set instead.
+template <bool RIGHT, bool D, bool SET, typename T>
+__device__ __forceinline__ void add_k(su3<T>& c, const su3<T>& k, const su3<T>& m) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      T re = SET ? T(0) : c.e[3 * i + j].re, im = SET ? T(0) : c.e[3 * i + j].im;
+      bool fresh = SET;
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        const cx<T> x = RIGHT ? elem<D>(m, i, l) : k.e[3 * i + l];
+        const cx<T> y = RIGHT ? k.e[3 * l + j] : elem<D>(m, l, j);
+        if (RIGHT ? l == j : l == i) {  // the imaginary diagonal: x.re (or y.re) is zero
+          const T a = RIGHT ? y.im : x.im;
+          const cx<T> b = RIGHT ? x : y;
+          re = fresh ? -a * b.im : fma(-a, b.im, re);
+          im = fresh ? a * b.re : fma(a, b.re, im);
+        } else {
+          re = fresh ? x.re * y.re : fma(x.re, y.re, re);
+          im = fresh ? x.re * y.im : fma(x.re, y.im, im);
+          re = fma(-x.im, y.im, re);
+          im = fma(x.im, y.re, im);
+        }
+        fresh = false;
+      }
+      c.e[3 * i + j] = cx<T>{re, im};
+    }
+}
+
 // C -= A B
 template <typename T>
 __device__ __forceinline__ void mac_neg(su3<T>& c, const su3<T>& a, const su3<T>& b) {
@@ -358,8 +390,9 @@ __device__ __forceinline__ void clover_plaquette(su3<T>& t, su3<T>& w, const WCt
   su3<T> ab, ax;
   {
     const su3<T> ub = c.template u<0, f1, f2, f3, 0>();  // b = ub^dagger
-    su3<T> x = mul<false, true>(c.template k<1, f1, f2, f3>(pair), ub);
-    mac<true, false>(x, ub, c.template k<0, f1, f2, f3>(pair));  // K2 b + b K3
+    su3<T> x;  // K2 b + b K3
+    add_k<false, true, true>(x, c.template k<1, f1, f2, f3>(pair), ub);
+    add_k<true, true, false>(x, c.template k<0, f1, f2, f3>(pair), ub);
     su3<T> a;
     if constexpr (S > 0)
       a = c.template u<1, 0, 0, 0, J>();
@@ -399,49 +432,83 @@ __device__ __forceinline__ void clover_plane(su3<T>& acc, const WCtx<T>& c0) {
   asm volatile("" : "+s"(c.U), "+s"(c.K));
   const int rho = c.ax[0], nu = c.ax[J];
   const int pair = rho < nu ? pair_index(rho, nu) : pair_index(nu, rho);
-  mac<false, false>(t, w, c.template k<0, 0, 0, 0>(pair));
-  mac<false, false>(t, c.template k<1, 0, 0, 0>(pair), w);
+  add_k<true, false, false>(t, c.template k<0, 0, 0, 0>(pair), w);
+  add_k<false, false, false>(t, c.template k<1, 0, 0, 0>(pair), w);
   axpy(acc, T(rho < nu ? 1 : -1), t);
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// FP32: two waves per SIMD (199 VGPRs); three would spill: 1.75 against 1.50 ms at
-// 32^3 x 64. FP64: one wave (256 VGPRs and 162 AGPRs). With one sum over s per plane and
-// projected spinors, FP32 1.63 -> 1.50 ms at 32^3 x 64, FP64 1.06 -> 0.95 ms at 24^3 x 48.
-// (abd as two rows with the third rebuilt would save another 2%, at an error against 64 bits
-// that is no longer below that of the separate plaquettes.)
 template <typename T>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1))) void wilson_force_kernel(Geom g, const T* __restrict__ U,
-                                                               const T* __restrict__ X, const T* __restrict__ Y,
-                                                               const T* __restrict__ K, T* __restrict__ out,
-                                                               double kappa, double csw, int ntiles) {
+__device__ __forceinline__ WCtx<T> make_wctx(const Geom& g, const T* U, const T* K, int mu, int p, int cb) {
+  WCtx<T> c;
+  int x[4];
+  cb_coords(g, p, cb, x);
+  c.U = U;
+  c.K = K;
+  c.Vh = g.Vh;
+  c.p = p;
+  c.ax[0] = mu;
+  c.ax[1] = mu == 0 ? 1 : 0;
+  c.ax[2] = mu <= 1 ? 2 : 1;
+  c.ax[3] = mu <= 2 ? 3 : 2;
+  Nbr full;
+  make_nbr(g, x, full);
+#pragma unroll
+  for (int fa = 0; fa < 4; ++fa) {
+    const int a = c.ax[fa];
+#pragma unroll
+    for (int dd = 0; dd < 5; ++dd)
+      c.nb.o[fa][dd] = a == 0 ? full.o[0][dd] : a == 1 ? full.o[1][dd] : a == 2 ? full.o[2][dd] : full.o[3][dd];
+  }
+  return c;
+}
+
+// The hopping outer products B' and C' of the link.
+template <typename T>
+__device__ __forceinline__ su3<T> hop_b(const WCtx<T>& c, const T* X, const T* Y, int cb) {
+  return outer(load_projected(X, c.p ^ 1, c.Vh, nbr_cb<1, 0, 0, 0>(c.nb), c.ax[0], T(-1)),
+               load_projected(Y, c.p, c.Vh, cb, c.ax[0], T(-1)));
+}
+template <typename T>
+__device__ __forceinline__ su3<T> hop_c(const WCtx<T>& c, const T* X, const T* Y, int cb) {
+  return outer(load_projected(X, c.p, c.Vh, cb, c.ax[0], T(1)),
+               load_projected(Y, c.p ^ 1, c.Vh, nbr_cb<1, 0, 0, 0>(c.nb), c.ax[0], T(1)));
+}
+
+// M = U (-2 kappa B' + w acc) + 2 kappa C' U^+, w = -c_sw kappa / 8: the inner factor, and the
+// result from M's two terms.
+template <typename T>
+__device__ __forceinline__ su3<T> wilson_inner(const su3<T>& Bp, const su3<T>& acc, double kappa, double csw) {
+  const T w = T(-csw * kappa / 8.0), mk = T(-2.0 * kappa);
+  su3<T> inner;
+#pragma unroll
+  for (int e = 0; e < 9; ++e) {
+    inner.e[e].re = fma(mk, Bp.e[e].re, w * acc.e[e].re);
+    inner.e[e].im = fma(mk, Bp.e[e].im, w * acc.e[e].im);
+  }
+  return inner;
+}
+template <typename T>
+__device__ __forceinline__ void store_wilson(const WCtx<T>& c, T* out, int cb, const su3<T>& u, const su3<T>& inner,
+                                             const su3<T>& cu, double kappa) {
+  su3<T> M = mul<false, false>(u, inner);
+  axpy(M, T(2.0 * kappa), cu);
+  store_link(block_ptr(out, c.ax[0], c.p, c.Vh), c.Vh, cb, ta_scaled(M, T(-0.5)));
+}
+
+// FP32: two waves per SIMD (199 VGPRs); three would spill: 1.75 against 1.50 ms at
+// 32^3 x 64. FP64: one wave (256 VGPRs and 162 AGPRs). With one sum over s per plane,
+// projected spinors and the insertions' zero parts left out, FP32 1.63 -> 1.46 ms at 32^3 x 64,
+// FP64 1.05 -> 0.96 ms at 24^3 x 48. (abd as two rows with the third rebuilt would save another
+// 2%, at an error against 64 bits that is no longer below that of the separate plaquettes.)
+template <typename T>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1))) void
+wilson_force_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ X, const T* __restrict__ Y,
+                    const T* __restrict__ K, T* __restrict__ out, double kappa, double csw, int ntiles) {
   const LinkTile lt = link_tile(g, blockIdx.x, ntiles);
   const int cb = lt.chunk * kBlock + threadIdx.x;
   if (cb >= g.Vh) return;
-  WCtx<T> c;
-  {
-    int x[4];
-    cb_coords(g, lt.p, cb, x);
-    c.U = U;
-    c.K = K;
-    c.Vh = g.Vh;
-    c.p = lt.p;
-    const int mu = lt.mu;
-    c.ax[0] = mu;
-    c.ax[1] = mu == 0 ? 1 : 0;
-    c.ax[2] = mu <= 1 ? 2 : 1;
-    c.ax[3] = mu <= 2 ? 3 : 2;
-    Nbr full;
-    make_nbr(g, x, full);
-#pragma unroll
-    for (int fa = 0; fa < 4; ++fa) {
-      const int a = c.ax[fa];
-#pragma unroll
-      for (int dd = 0; dd < 5; ++dd)
-        c.nb.o[fa][dd] = a == 0 ? full.o[0][dd] : a == 1 ? full.o[1][dd] : a == 2 ? full.o[2][dd] : full.o[3][dd];
-    }
-  }
-  const int rho = lt.mu;
+  const WCtx<T> c = make_wctx(g, U, K, lt.mu, lt.p, cb);
 
   // clover leaves through the link
   su3<T> acc;
@@ -451,26 +518,51 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
     clover_plane<2>(acc, c);
     clover_plane<3>(acc, c);
   }
-  // M = U (-2 kappa B' + w acc) + 2 kappa C' U^+, w = -c_sw kappa / 8
-  const int pr = lt.p ^ 1;
-  const int cbr = nbr_cb<1, 0, 0, 0>(c.nb);
-  const T w = T(-csw * kappa / 8.0), mk = T(-2.0 * kappa);
-  su3<T> inner;
-  {
-    const su3<T> Bp = outer(load_projected(X, pr, g.Vh, cbr, rho, T(-1)), load_projected(Y, lt.p, g.Vh, cb, rho, T(-1)));
-#pragma unroll
-    for (int e = 0; e < 9; ++e) {
-      inner.e[e].re = fma(mk, Bp.e[e].re, w * acc.e[e].re);
-      inner.e[e].im = fma(mk, Bp.e[e].im, w * acc.e[e].im);
+  const su3<T> inner = wilson_inner(hop_b(c, X, Y, cb), acc, kappa, csw);
+  __builtin_amdgcn_sched_barrier(0);
+  const su3<T> Cp = hop_c(c, X, Y, cb);
+  const su3<T> u = c.template u<0, 0, 0, 0, 0>();
+  store_wilson(c, out, cb, u, inner, mul<false, true>(Cp, u), kappa);
+}
+
+// Small lattices: four waves share 64 links (one per lane of every wave), waves 0..2 the
+// clover leaves of a plane each, wave 3 the hopping terms, joined in LDS. With a wave per 64
+// links the clover term is a serial stream of 5,500 instructions whatever the lattice. The
+// same operations in the same order: bitwise the same force. It pays up to two workgroups
+// per CU: 4^4 FP32 20 -> 9 us, FP64 21 -> 11 us; 8^3 x 16 (512 workgroups) 22 -> 13 and 26 -> 21 us.
+template <typename T>
+__global__ __launch_bounds__(256) void wilson_force_small_kernel(Geom g, const T* __restrict__ U,
+                                                                 const T* __restrict__ X, const T* __restrict__ Y,
+                                                                 const T* __restrict__ K, T* __restrict__ out,
+                                                                 double kappa, double csw) {
+  __shared__ T lds[4 * 18 * 64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const LdsMats<T> m{lds, (int)(threadIdx.x & 63)};
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const bool active = (tile >> 3) * 64 + m.lane < g.Vh;
+  const int cb = active ? (tile >> 3) * 64 + m.lane : 0;
+  const WCtx<T> c = make_wctx(g, U, K, tile & 3, (tile >> 2) & 1, cb);
+  su3<T> acc;
+  set_zero(acc);
+  if (active) {
+    if (wave == 0) {
+      clover_plane<1>(acc, c);
+    } else if (wave == 1) {
+      clover_plane<2>(acc, c);
+      m.put(0, acc);
+    } else if (wave == 2) {
+      clover_plane<3>(acc, c);
+      m.put(1, acc);
+    } else {
+      m.put(2, hop_b(c, X, Y, cb));
+      m.put(3, mul<false, true>(hop_c(c, X, Y, cb), c.template u<0, 0, 0, 0, 0>()));
     }
   }
-  __builtin_amdgcn_sched_barrier(0);
-  const su3<T> Cp = outer(load_projected(X, lt.p, g.Vh, cb, rho, T(1)), load_projected(Y, pr, g.Vh, cbr, rho, T(1)));
-  const su3<T> u = c.template u<0, 0, 0, 0, 0>();
-  su3<T> M = mul<false, false>(u, inner);
-  su3<T> cu = mul<false, true>(Cp, u);
-  axpy(M, T(2.0 * kappa), cu);
-  store_link(block_ptr(out, rho, lt.p, g.Vh), g.Vh, cb, ta_scaled(M, T(-0.5)));
+  __syncthreads();
+  if (!active || wave != 0) return;
+  add(acc, m.get(0));
+  add(acc, m.get(1));
+  store_wilson(c, out, cb, c.template u<0, 0, 0, 0, 0>(), wilson_inner(m.get(2), acc, kappa, csw), m.get(3), kappa);
 }
 
 }  // namespace
@@ -485,6 +577,10 @@ hipError_t launch_wilson_clover(const Geom& g, const T* X, const T* Y, T* K, hip
 template <typename T>
 hipError_t launch_wilson_force(const Geom& g, const T* U, const T* X, const T* Y, const T* K, T* out, double kappa,
                                double csw, hipStream_t s) {
+  if (csw != 0.0 && link_tiles(g, 64) <= 2 * kCUs) {
+    wilson_force_small_kernel<T><<<link_tiles(g, 64), 256, 0, s>>>(g, U, X, Y, K, out, kappa, csw);
+    return hipGetLastError();
+  }
   const int nt = link_tiles(g);
   wilson_force_kernel<T><<<nt, kBlock, 0, s>>>(g, U, X, Y, K, out, kappa, csw, nt);
   return hipGetLastError();
