@@ -213,8 +213,14 @@ bool use_factored() {
   return a == SYM_ALG_FACTORED || a == SYM_ALG_AUTO;
 }
 
+// Kinetic-energy partials of the force pass (a double per workgroup): the first staple slot,
+// direction x along axis x, which no staple has (6 V/2 complex numbers, far more than the
+// workgroups).
+double* force_kin(const Workspace& w) { return static_cast<double*>(w.staples); }
+
 // One force evaluation; G goes to `out` (Store) or is subtracted, times `kick`, from the
-// momenta in `out` (Kick). With act != nullptr the per-workgroup staple partials go there.
+// momenta in `out` (Kick). With act != nullptr the per-workgroup staple partials go there;
+// with KickOld or KickNew (factored only) the kinetic-energy partials go to force_kin(w).
 template <typename T>
 hipError_t force_into(bool factored, const Geom& g, const T* U, T* out, double kick, double* act, const Coeffs& c,
                       ForceOut mode, const Workspace& w, hipStream_t s) {
@@ -223,7 +229,7 @@ hipError_t force_into(bool factored, const Geom& g, const T* U, T* out, double k
     hipError_t e = timed("staples", s, [&] { return sym::launch_staples<T>(g, U, S8, s); });
     if (e != hipSuccess) return e;
     return timed("force_factored", s,
-                 [&] { return sym::launch_force_factored<T>(g, U, S8, out, kick, act, c, mode, s); });
+                 [&] { return sym::launch_force_factored<T>(g, U, S8, out, kick, act, force_kin(w), c, mode, s); });
   }
   return timed("force_direct", s, [&] { return sym::launch_force_direct<T>(g, U, out, kick, act, c, mode, s); });
 }
@@ -295,26 +301,34 @@ int do_leapfrog(bool factored, const Geom& g, const Coeffs& c, void* Uv, void* P
     return hip_status(e);
   }
   // The first force pass sees U at the start and the last one U at the end: their
-  // fused action partials give S for H, with the kinetic energy of P taken before the
-  // first kick and after the last.
+  // fused action partials give S for H. The factored passes also sum the kinetic energy of
+  // the momenta they kick, before the first kick and after the last (a pass over P less at
+  // either end: FP64 24^3 x 48 76 us each, 8^4 a launch); with the direct form a kernel of its
+  // own does.
+  const bool fused = factored && H_dev;
   auto finish_h = [&](double* out) {
     return timed("finish", s, [&] {
-      return sym::launch_finish_hamiltonian(w.act, force_tiles<T>(factored, g), force_kind(factored), w.kin,
-                                            sym::link_tiles(g), g, c, w.stage, out, s);
+      return sym::launch_finish_hamiltonian(w.act, force_tiles<T>(factored, g), force_kind(factored),
+                                            fused ? force_kin(w) : w.kin,
+                                            fused ? force_tiles<T>(factored, g) : sym::link_tiles(g), g, c, w.stage,
+                                            out, s);
     });
   };
+  auto kinetic = [&] { return timed("kinetic", s, [&] { return sym::launch_kinetic<T>(g, P, w.kin, s); }); };
   double* act = H_dev ? w.act : nullptr;
-  if (H_dev) e = timed("kinetic", s, [&] { return sym::launch_kinetic<T>(g, P, w.kin, s); });
-  if (e == hipSuccess) e = force_into<T>(factored, g, U, P, 0.5 * dt, act, c, ForceOut::Kick, w, s);
+  if (H_dev && !fused) e = kinetic();
+  if (e == hipSuccess)
+    e = force_into<T>(factored, g, U, P, 0.5 * dt, act, c, fused ? ForceOut::KickOld : ForceOut::Kick, w, s);
   if (H_dev && e == hipSuccess) e = finish_h(H_dev);
   for (int it = 0; it < nsteps && e == hipSuccess; ++it) {
     e = timed("drift", s, [&] { return sym::launch_drift<T>(g, U, P, dt, s); });
     if (e == hipSuccess) {
       const bool last = it + 1 == nsteps;
-      e = force_into<T>(factored, g, U, P, last ? 0.5 * dt : dt, last ? act : nullptr, c, ForceOut::Kick, w, s);
+      e = force_into<T>(factored, g, U, P, last ? 0.5 * dt : dt, last ? act : nullptr, c,
+                        last && fused ? ForceOut::KickNew : ForceOut::Kick, w, s);
     }
   }
-  if (H_dev && e == hipSuccess) e = timed("kinetic", s, [&] { return sym::launch_kinetic<T>(g, P, w.kin, s); });
+  if (H_dev && !fused && e == hipSuccess) e = kinetic();
   if (H_dev && e == hipSuccess) e = finish_h(H_dev + 1);
   return hip_status(e);
 }

@@ -497,6 +497,7 @@ struct FState {
   su3<T> tP, RA, RB, t, QA, QB;
   double part;  // Re tr(U t) before the short-side rectangles and cubes are added
   double a[3];
+  double kin;    // kinetic energy of the link's momentum (KickOld, KickNew)
   T cP, cR, cC;
   double beta, kick;
   T* out;
@@ -672,11 +673,13 @@ __device__ __forceinline__ void use_fstep(FState<T>& st, const D& d) {
       store_link(dst, st.Vh, st.cb, gr);
     } else {
       su3<T> q = load_link(static_cast<const cx<T>*>(dst), st.Vh, st.cb);
+      if constexpr (MODE == ForceOut::KickOld) st.kin = kinetic_of(q);
 #pragma unroll
       for (int e = 0; e < 9; ++e) {
         q.e[e].re = T(double(q.e[e].re) - st.kick * double(G.e[e].re));
         q.e[e].im = T(double(q.e[e].im) - st.kick * double(G.e[e].im));
       }
+      if constexpr (MODE == ForceOut::KickNew) st.kin = kinetic_of(q);
       store_link(dst, st.Vh, st.cb, q);
     }
   }
@@ -716,12 +719,14 @@ __device__ __forceinline__ void link_state(const Geom& g, const T* U, const T* S
   st.mu = mu;
   st.p = p;
   st.cb = cb;
+  st.kin = 0.0;
 }
 
-// Pass 2 for link (mu, p, cb): force epilogue per MODE, deficit partials into a[3].
+// Pass 2 for link (mu, p, cb): force epilogue per MODE, deficit partials into a[0..2], the
+// kinetic energy (KickOld, KickNew) into a[3].
 template <typename T, ForceOut MODE>
 __device__ __forceinline__ void factored_link(const Geom& g, const T* U, const T* S8, T* out, double kick,
-                                              const Coeffs& cf, int mu, int p, int cb, double a[3]) {
+                                              const Coeffs& cf, int mu, int p, int cb, double* a) {
   FCtx<T> c;
   FState<T> st;
   link_state(g, U, S8, out, kick, cf, mu, p, cb, c, st);
@@ -731,6 +736,7 @@ __device__ __forceinline__ void factored_link(const Geom& g, const T* U, const T
   a[0] = st.a[0];
   a[1] = st.a[1];
   a[2] = st.a[2];
+  if constexpr (with_kinetic(MODE)) a[3] = st.kin;
 }
 
 // ------------------------------------------------- pass 2 on small lattices
@@ -923,11 +929,11 @@ __device__ __forceinline__ void small_row(const FCtx<T>& c, const FState<T>& st,
 }
 
 // One wave's part of link (mu, p, cb): `wave` is wave-uniform, `active` false for lanes past
-// the lattice (they only take part in the barriers). a[3] is set by wave 0's active lanes.
+// the lattice (they only take part in the barriers). a is set by wave 0's active lanes.
 template <typename T, ForceOut MODE>
 __device__ __forceinline__ void factored_link_small(const Geom& g, const T* U, const T* S8, T* out, double kick,
                                                     const Coeffs& cf, int mu, int p, int cb, bool active, int wave,
-                                                    const LdsMats<T>& m, double a[3]) {
+                                                    const LdsMats<T>& m, double* a) {
   FCtx<T> c;
   FState<T> st;
   link_state(g, U, S8, out, kick, cf, mu, p, cb, c, st);
@@ -964,6 +970,7 @@ __device__ __forceinline__ void factored_link_small(const Geom& g, const T* U, c
     a[0] = st.a[0];
     a[1] = st.a[1];
     a[2] = st.a[2];
+    if constexpr (with_kinetic(MODE)) a[3] = st.kin;
   }
 }
 

@@ -16,18 +16,37 @@ __global__ __launch_bounds__(kBlock) void staples_kernel(Geom g, const T* __rest
   if (cb < g.Vh) staples_site(g, U, S8, st.p, cb);
 }
 
+// The workgroup's partials: the three deficit sums and, with KickOld and KickNew, the kinetic
+// energy (both are written by those; either pointer may be null otherwise).
+template <ForceOut MODE>
+__device__ __forceinline__ void store_partials(double (&a)[4], double* __restrict__ partials,
+                                               double* __restrict__ kin) {
+  if constexpr (with_kinetic(MODE)) {
+    block_sum<4>(a);
+    if (threadIdx.x == 0) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) partials[3 * (size_t)blockIdx.x + k] = a[k];
+      kin[blockIdx.x] = a[3];
+    }
+  } else if (partials != nullptr) {
+    double b[3] = {a[0], a[1], a[2]};
+    block_sum_store<3>(b, partials + 3 * (size_t)blockIdx.x);
+  }
+}
+
 template <typename T, ForceOut MODE>
 __global__ __launch_bounds__(factored_links<T>()) void force_factored_kernel(Geom g, const T* __restrict__ U,
                                                                              const T* __restrict__ S8,
                                                                              T* __restrict__ out, double kick,
-                                                                             double* __restrict__ partials, Coeffs cf,
+                                                                             double* __restrict__ partials,
+                                                                             double* __restrict__ kin, Coeffs cf,
                                                                              int ntiles) {
   constexpr int N = factored_links<T>();
   const LinkTile lt = force_tile(g, blockIdx.x, ntiles, N);
   const int cb = lt.chunk * N + threadIdx.x;
-  double a[3] = {0.0, 0.0, 0.0};
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
   if (cb < g.Vh) factored_link<T, MODE>(g, U, S8, out, kick, cf, lt.mu, lt.p, cb, a);
-  if (partials != nullptr) block_sum_store<3>(a, partials + 3 * (size_t)blockIdx.x);
+  store_partials<MODE>(a, partials, kin);
 }
 
 // Small lattices: a wave per site chunk and step of the staples, and eight waves per 64
@@ -44,6 +63,7 @@ __global__ __launch_bounds__(64 * factored::kSmallWaves) void force_small_kernel
                                                                                  const T* __restrict__ S8,
                                                                                  T* __restrict__ out, double kick,
                                                                                  double* __restrict__ partials,
+                                                                                 double* __restrict__ kin,
                                                                                  Coeffs cf) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -51,18 +71,23 @@ __global__ __launch_bounds__(64 * factored::kSmallWaves) void force_small_kernel
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int cb = (tile >> 3) * 64 + m.lane;
   const bool active = cb < g.Vh;
-  double a[3] = {0.0, 0.0, 0.0};
+  double a[4] = {0.0, 0.0, 0.0, 0.0};
   factored::factored_link_small<T, MODE>(g, U, S8, out, kick, cf, tile & 3, (tile >> 2) & 1, active ? cb : 0, active,
                                          wave, m, a);
-  if (partials != nullptr) block_sum_store<3>(a, partials + 3 * (size_t)blockIdx.x);
+  store_partials<MODE>(a, partials, kin);
 }
 
 template <typename T, ForceOut MODE>
-hipError_t force_small(const Geom& g, const T* U, const T* S8, T* out, double kick, double* partials, const Coeffs& c,
-                       hipStream_t s) {
+hipError_t launch_mode(const Geom& g, const T* U, const T* S8, T* out, double kick, double* partials, double* kin,
+                       const Coeffs& c, hipStream_t s) {
   const int nt = factored_tiles<T>(g);
-  force_small_kernel<T, MODE><<<nt, 64 * factored::kSmallWaves, factored::small_lds_bytes<T>(), s>>>(
-      g, U, S8, out, kick, partials, c);
+  if (force_is_small(g))
+    force_small_kernel<T, MODE><<<nt, 64 * factored::kSmallWaves, factored::small_lds_bytes<T>(), s>>>(
+        g, U, S8, out, kick, partials, kin, c);
+  else
+    // one or two waves per SIMD by registers (FP64, FP32); no LDS reservation: with
+    // workgroups of one or two waves it would only take waves away
+    force_factored_kernel<T, MODE><<<nt, factored_links<T>(), 0, s>>>(g, U, S8, out, kick, partials, kin, c, nt);
   return hipGetLastError();
 }
 
@@ -82,23 +107,19 @@ hipError_t launch_staples(const Geom& g, const T* U, T* S8, hipStream_t s) {
 
 template <typename T>
 hipError_t launch_force_factored(const Geom& g, const T* U, const T* S8, T* out, double kick, double* partials,
-                                 const Coeffs& c, ForceOut mode, hipStream_t s) {
-  if (force_is_small(g)) {
-    if (mode == ForceOut::Store) return force_small<T, ForceOut::Store>(g, U, S8, out, kick, partials, c, s);
-    if (mode == ForceOut::Kick) return force_small<T, ForceOut::Kick>(g, U, S8, out, kick, partials, c, s);
-    return force_small<T, ForceOut::Grad>(g, U, S8, out, kick, partials, c, s);
+                                 double* kin, const Coeffs& c, ForceOut mode, hipStream_t s) {
+  switch (mode) {
+    case ForceOut::Store:
+      return launch_mode<T, ForceOut::Store>(g, U, S8, out, kick, partials, kin, c, s);
+    case ForceOut::Kick:
+      return launch_mode<T, ForceOut::Kick>(g, U, S8, out, kick, partials, kin, c, s);
+    case ForceOut::Grad:
+      return launch_mode<T, ForceOut::Grad>(g, U, S8, out, kick, partials, kin, c, s);
+    case ForceOut::KickOld:
+      return launch_mode<T, ForceOut::KickOld>(g, U, S8, out, kick, partials, kin, c, s);
+    default:
+      return launch_mode<T, ForceOut::KickNew>(g, U, S8, out, kick, partials, kin, c, s);
   }
-  const int nt = factored_tiles<T>(g);
-  constexpr int N = factored_links<T>();
-  // one or two waves per SIMD by registers (FP64, FP32); no LDS reservation: with
-  // workgroups of one or two waves it would only take waves away
-  if (mode == ForceOut::Store)
-    force_factored_kernel<T, ForceOut::Store><<<nt, N, 0, s>>>(g, U, S8, out, kick, partials, c, nt);
-  else if (mode == ForceOut::Kick)
-    force_factored_kernel<T, ForceOut::Kick><<<nt, N, 0, s>>>(g, U, S8, out, kick, partials, c, nt);
-  else
-    force_factored_kernel<T, ForceOut::Grad><<<nt, N, 0, s>>>(g, U, S8, out, kick, partials, c, nt);
-  return hipGetLastError();
 }
 
 #ifndef SYM_ONLY_F64
@@ -109,11 +130,11 @@ template hipError_t launch_staples<double>(const Geom&, const double*, double*, 
 #endif
 #ifndef SYM_ONLY_F64
 template hipError_t launch_force_factored<float>(const Geom&, const float*, const float*, float*, double, double*,
-                                                 const Coeffs&, ForceOut, hipStream_t);
+                                                 double*, const Coeffs&, ForceOut, hipStream_t);
 #endif
 #ifndef SYM_ONLY_F32
 template hipError_t launch_force_factored<double>(const Geom&, const double*, const double*, double*, double, double*,
-                                                  const Coeffs&, ForceOut, hipStream_t);
+                                                  double*, const Coeffs&, ForceOut, hipStream_t);
 #endif
 
 }  // namespace sym

@@ -19,7 +19,10 @@ struct Coeffs {
 // What a force kernel does with G = (beta/6)(U t)_TA: store it, subtract kick * G from
 // the momenta in `out`, or store the gradient of S_G with respect to U projected on the
 // tangent space of SU(3) at U, 2 G U (see sym_action_grad).
-enum class ForceOut { Store = 0, Kick = 1, Grad = 2 };
+// KickOld and KickNew (factored passes only): Kick, with the kinetic energy of the momenta
+// before or after it.
+enum class ForceOut { Store = 0, Kick = 1, Grad = 2, KickOld = 3, KickNew = 4 };
+constexpr bool with_kinetic(ForceOut m) { return m == ForceOut::KickOld || m == ForceOut::KickNew; }
 
 // Number of workgroups of a per-link launch (a multiple of 8: 4 directions x 2 parities)
 // with `links` links (threads) per workgroup.
@@ -81,9 +84,10 @@ constexpr size_t factored_lds_reservation() {
 }
 template <typename T>
 hipError_t launch_staples(const Geom& g, const T* U, T* S8, hipStream_t s);
+// kin: with KickOld and KickNew, one kinetic-energy partial per workgroup.
 template <typename T>
-hipError_t launch_force_factored(const Geom& g, const T* U, const T* S8, T* out, double kick,
-                                 double* partials, const Coeffs& c, ForceOut mode, hipStream_t s);
+hipError_t launch_force_factored(const Geom& g, const T* U, const T* S8, T* out, double kick, double* partials,
+                                 double* kin, const Coeffs& c, ForceOut mode, hipStream_t s);
 
 // Batched factored force over many independent lattices (force_batch.hip). The work
 // table travels by value in the kernel arguments, so a captured launch holds no host

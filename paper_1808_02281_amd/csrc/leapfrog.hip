@@ -122,15 +122,7 @@ __global__ __launch_bounds__(kBlock) void kinetic_kernel(Geom g, const T* __rest
   const int mu = lt.mu, p = lt.p, chunk = lt.chunk;
   const int cb = chunk * kBlock + threadIdx.x;
   double v[1] = {0.0};
-  if (cb < g.Vh) {
-    const su3<double> q = to_double(load_link(block_ptr(P, mu, p, g.Vh), g.Vh, cb));
-    double s = 0.0;  // -Re tr(Pi^2) = -sum_ij Re(Pi_ij Pi_ji)
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) s -= q.e[3 * i + j].re * q.e[3 * j + i].re - q.e[3 * i + j].im * q.e[3 * j + i].im;
-    v[0] = s;
-  }
+  if (cb < g.Vh) v[0] = kinetic_of(load_link(block_ptr(P, mu, p, g.Vh), g.Vh, cb));
   block_sum_store<1>(v, partials + blockIdx.x);
 }
 

@@ -126,6 +126,18 @@ __device__ __forceinline__ double re_tr(const su3<T>& a) {
   return double(a.e[0].re) + double(a.e[4].re) + double(a.e[8].re);
 }
 
+// -Re tr(Q^2) in double: the kinetic energy of the momentum matrix Q.
+template <typename T>
+__device__ __forceinline__ double kinetic_of(const su3<T>& q) {
+  double s = 0.0;
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      s -= double(q.e[3 * i + j].re) * double(q.e[3 * j + i].re) - double(q.e[3 * i + j].im) * double(q.e[3 * j + i].im);
+  return s;
+}
+
 // scale * B_TA with B_TA = (B - B^dagger)/2 - tr(B - B^dagger)/6 * I (eq. 18_6_6_11).
 template <typename T>
 __device__ __forceinline__ su3<T> ta_scaled(const su3<T>& b, T scale) {
