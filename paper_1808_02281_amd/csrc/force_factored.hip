@@ -42,8 +42,8 @@ __global__ __launch_bounds__(factored_links<T>()) void force_factored_kernel(Geo
                                                                              double* __restrict__ kin, Coeffs cf,
                                                                              int ntiles) {
   constexpr int N = factored_links<T>();
-  const LinkTile lt = force_tile(g, blockIdx.x, ntiles, N);
-  const int cb = lt.chunk * N + threadIdx.x;
+  const LinkSite lt = force_site<N>(g, blockIdx.x, ntiles, threadIdx.x);
+  const int cb = lt.cb;
   double a[4] = {0.0, 0.0, 0.0, 0.0};
   if (cb < g.Vh) factored_link<T, MODE>(g, U, S8, out, kick, cf, lt.mu, lt.p, cb, a);
   store_partials<MODE>(a, partials, kin);

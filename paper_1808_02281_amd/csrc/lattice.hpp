@@ -240,7 +240,7 @@ __device__ __forceinline__ LinkTile link_tile(const Geom& g, int linear, int nti
 // FP32 2.33 -> 2.15 ms, FP64 4.95 -> 4.22 ms. That needs chunks that lie in one (x, y) plane;
 // where a plane is not whole chunks the z-neighbours of a chunk straddle two others, and
 // the same walk over rounded plane sizes was slower (24^3 x 48: FP64 1.57 -> 1.89 ms, FP32
-// 0.70 -> 0.71 ms): such lattices keep link_tile.
+// 0.70 -> 0.71 ms): such lattices keep link_tile, or in FP64 take half chunks (force_site).
 __device__ __forceinline__ bool planes_are_chunks(const Geom& g, int n) { return g.Lxh * g.L[1] % n == 0; }
 
 // The chunk of n sites at position k of the walk (planes_are_chunks(g, n) holds).
@@ -266,6 +266,39 @@ __device__ __forceinline__ LinkTile force_tile(const Geom& g, int linear, int nt
   r.p = (tile >> 2) & 1;
   r.chunk = walk_chunk(g, n, (g.L[3] + 7) >> 3, tile >> 3);
   return r;
+}
+
+// The link of a thread of the factored force pass, N links per workgroup. Where a plane is
+// an odd number of half chunks (24 x 24, 40 x 40), a workgroup of 64 takes half a chunk of two
+// z-neighbouring planes (Lz is even), so that its z-neighbours are whole workgroups again;
+// runs of 32 links are still 512 B of every matrix element in FP64. The pairs of planes are
+// walked t through the XCD's slab fastest, then y, then z. Against link_tile: FP64 24^3 x 48
+// 1.51 -> 1.43 ms, 24^2 x 40^2 2.04 -> 1.90, 56 x 40 x 16 x 24 2.02 -> 1.91; y last, as in
+// walk_chunk, 1.47 and 2.00 ms. For planes of whole chunks this order loses (FP64 32^3 x 64
+// 4.26 -> 4.53 ms), as do runs of 16 (24^3 x 48 1.51). FP32, whose workgroups of 128 would need
+// quarter chunks of four planes, gains 1% (0.708 -> 0.700 ms) and keeps link_tile.
+struct LinkSite {
+  int mu, p, cb;
+};
+
+template <int N>
+__device__ __forceinline__ LinkSite force_site(const Geom& g, int linear, int ntiles, int lane) {
+  const int plane = g.Lxh * g.L[1];
+  if (N != 64 || plane % 64 != 32) {
+    const LinkTile lt = force_tile(g, linear, ntiles, N);
+    return LinkSite{lt.mu, lt.p, lt.chunk * N + lane};
+  }
+  const int tile = xcd_tile(linear, ntiles);
+  const int slab = (g.L[3] + 7) >> 3, Ly = plane >> 5, Lz = g.L[2] >> 1, Lt = g.L[3];
+  int k = tile >> 3;
+  const int t0 = k / (slab * Lz * Ly) * slab;
+  const int tn = min(slab, Lt - t0);
+  k -= t0 * Lz * Ly;
+  const int z = k / (Ly * tn);
+  k -= z * Ly * tn;
+  const int y = k / tn, t = t0 + k - y * tn;
+  const int cb = plane * (2 * z + (lane >> 5) + g.L[2] * t) + 32 * y + (lane & 31);
+  return LinkSite{tile & 3, (tile >> 2) & 1, cb};
 }
 
 // Per-site kernels (one thread per site of one parity): workgroup -> (parity,

@@ -1,6 +1,6 @@
 """The factored force on lattices whose (x, y) planes are whole workgroups (the blocked walk
 over z and t), with remainders of every part of the walk, against the FP64 oracle on every
-link; FP32 planes of one and two workgroups, FP64 of two and four. Gates as in the parity
+link; FP32 planes of one and two workgroups, FP64 of two and four and of one and three halves. Gates as in the parity
 tests: 1e-12 and 1e-5 of the largest force, the FP32 oracle on the rounded links."""
 import pytest
 
@@ -18,6 +18,8 @@ SHAPES = [
     (16, 16, 4, 4),    # one block of z, slabs of one t-slice on four of the eight XCDs
     (32, 8, 6, 10),    # a block of two z, slabs of two t-slices, the last XCDs' share uneven
     (16, 32, 10, 18),  # two chunks (FP32) a plane, blocks 4 4 2 of z, slabs of three
+    (8, 8, 10, 14),    # FP64: one half workgroup a plane, slabs of two
+    (8, 24, 6, 18),    # FP64: three half workgroups a plane, slabs of three
 ]
 
 
