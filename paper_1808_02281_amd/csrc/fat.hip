@@ -14,17 +14,57 @@ namespace {
 // force pass (force_tile) with the parity fastest, so that the two parities of a chunk, which
 // read each other's fields, run side by side. These passes are bound by field data from
 // beyond the L2. FP32 at 32^3 x 64, against direction fastest in t-fastest slabs: FK2 2.65 ->
-// 2.56, FK3 1.44 -> 1.38, BK2 2.89 -> 2.88, GK 7.04 -> 6.73 ms (FK1, which reads links only, was
-// slower, 1.06 -> 1.12 ms, and keeps link_tile, as does BK3); 24^3 x 48, where the walk does not
-// apply and only the parity moves: 0.835 -> 0.810, 0.456 -> 0.451, 0.921 -> 0.908, 2.13 -> 2.11 ms.
-// FP64 at 32^4: FK2 2.23 -> 2.19, FK3 1.34 -> 1.26, BK2 2.62 -> 2.60 ms, but GK 6.40 -> 6.73 ms: the FP64
-// gather keeps link_tile.
+// 2.56, FK3 1.44 -> 1.38, BK2 2.89 -> 2.88 ms (FK1, which reads links only, was slower, 1.06 ->
+// 1.12 ms, and keeps link_tile, as does BK3); 24^3 x 48, where the walk does not apply and only
+// the parity moves: 0.835 -> 0.810, 0.456 -> 0.451, 0.921 -> 0.908 ms, and GK, which in FP32
+// keeps this order there, 2.13 -> 2.11 ms.
+// FP64 at 32^4: FK2 2.23 -> 2.19, FK3 1.34 -> 1.26, BK2 2.62 -> 2.60 ms.
 __device__ __forceinline__ LinkTile fat_tile(const Geom& g, int linear, int ntiles) {
   LinkTile lt = force_tile(g, linear, ntiles, kBlock);
   const int q = lt.p * 4 + lt.mu;
   lt.p = q & 1;
   lt.mu = q >> 1;
   return lt;
+}
+
+// The link of a thread of the gradient gather GK, which reads the most fields: a workgroup of
+// four waves takes 64 links in each of four z-neighbouring planes (or 128 in each of two),
+// whose transports along z then meet in one CU's L1 and at the same time in the L2; parity
+// fastest, then direction, t through the XCD's slab, y, z. Against fat_tile, FP32: 32^3 x 64
+// 6.67 -> 6.43, 32 x 24^2 x 32 1.80 -> 1.73 ms; against link_tile, FP64: 32^4 6.27 -> 5.55,
+// 32 x 24^2 x 32 3.49 -> 3.15, 32 x 16 x 32 x 16 1.50 -> 1.40, 32 x 16^2 x 48 2.37 -> 2.34 ms. FP64
+// planes below a workgroup (16^3 x 32) take 0.685 ms in fours, 0.665 in twos, which is where
+// they were. Planes that are not whole runs of 64 gain nothing from eight planes of 32 links
+// (FP64 24^4 1.94 ms either way) and keep the orders named. The other passes lose by the blocks
+// on some lattices what they gain on others (FP64 FK2 and BK2 at 32^4 2.18 -> 2.06 and 2.59 ->
+// 2.48, at 32 x 16^2 x 48 0.79 -> 0.83 and 0.93 -> 1.03 ms).
+template <typename T>
+__device__ __forceinline__ int gk_planes(const Geom& g) {
+  const int plane = g.Lxh * g.L[1];
+  if (plane % 64 == 0 && g.L[2] % 4 == 0 && (sizeof(T) == 4 || plane >= kBlock)) return 4;
+  return plane % 128 == 0 ? 2 : 0;  // Lz is even
+}
+
+template <typename T>
+__device__ __forceinline__ LinkSite gk_site(const Geom& g, int linear, int ntiles) {
+  const int lane = threadIdx.x;
+  const int m = gk_planes<T>(g);
+  if (m == 0) {
+    const LinkTile lt = sizeof(T) == 4 ? fat_tile(g, linear, ntiles) : link_tile(g, linear, ntiles);
+    return LinkSite{lt.mu, lt.p, lt.chunk * kBlock + lane};
+  }
+  const int tile = xcd_tile(linear, ntiles);
+  const int run = kBlock / m, plane = g.Lxh * g.L[1];
+  const int slab = (g.L[3] + 7) >> 3, Ly = plane / run, Lz = g.L[2] / m, Lt = g.L[3];
+  int k = tile >> 3;
+  const int t0 = k / (slab * Lz * Ly) * slab;
+  const int tn = min(slab, Lt - t0);
+  k -= t0 * Lz * Ly;
+  const int z = k / (Ly * tn);
+  k -= z * Ly * tn;
+  const int y = k / tn, t = t0 + k - y * tn;
+  const int cb = plane * (m * z + lane / run + g.L[2] * t) + run * y + lane % run;
+  return LinkSite{(tile >> 1) & 3, tile & 1, cb};
 }
 
 template <typename T>
@@ -185,8 +225,8 @@ template <typename T, int MODE>
 __global__ __launch_bounds__(kBlock) void fat_gk_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
                                                          const T* __restrict__ GW, Fields<T> w, T* __restrict__ out,
                                                          FatCoeffs cf, int ntiles) {
-  const LinkTile lt = sizeof(T) == 4 ? fat_tile(g, blockIdx.x, ntiles) : link_tile(g, blockIdx.x, ntiles);
-  const int cb = lt.chunk * kBlock + threadIdx.x;
+  const LinkSite lt = gk_site<T>(g, blockIdx.x, ntiles);
+  const int cb = lt.cb;
   if (cb >= g.Vh) return;
   Ctx<T> c;
   fat::make_ctx(g, U, lt.mu, lt.p, cb, c);

@@ -18,7 +18,9 @@ SHAPES = [
     (4, 6, 4, 10),   # shared links, half a wave past the lattice
     (8, 8, 8, 16),   # the largest with shared links
     (8, 8, 8, 18),   # the first without
-    (16, 32, 6, 4),  # tile walk, blocks of four and two z
+    (16, 32, 6, 4),  # tile walk, blocks of four and two z; gather in workgroups of two planes
+    (16, 8, 8, 10),  # gather in workgroups of four planes (FP32) or none, slabs of two t
+    (32, 16, 4, 6),  # of four planes, slabs of one t on six XCDs
 ]
 
 
