@@ -30,7 +30,7 @@ WORKLOAD = "thermal_32x32x32x64"
 # matrix 216), each figure stated beside its constant.
 FLOP_PAPER = 36770          # the paper's algorithm: 180 staple products, sums, U t, TA
 FLOP_STAPLES = 2079         # factored pass 1: 42 products per site (10.5 per link)
-FLOP_FACTORED = 12909       # factored pass 2: 57 products, 55 accumulations, weights, traces, TA
+FLOP_FACTORED = 12639       # factored pass 2: 57 products, 40 accumulations, weights, traces, TA
 FLOP_DIRECT = 36940         # direct kernel: 181 products + sums, traces, TA
 # Minimum HBM bytes per link of each kernel (read once / write once), per real size r.
 BYTES_STAPLES = lambda r: (12 + 6 * 12) * r              # read U (two rows), write 6 two-row staples
@@ -46,12 +46,12 @@ FAT_FLOP = {"fat_fk1": 2754, "fat_fk2": 7722, "fat_fk3": 2916, "fat_bk3": 2538, 
 FAT_MATRICES = {"fat_fk1": 4, "fat_fk2": 10, "fat_fk3": 9, "fat_bk3": 5, "fat_bk2": 12, "fat_gk": 22}
 C_ASQTAD = (5 / 8, -1 / 16, 1 / 64, -1 / 384, -1 / 16, -1 / 24)
 
-# Wilson-clover force, flop per link (force kernel: 6 clover plaquettes of 8 products
-# each with the insertions, hopping outer products, U B' and C' U^+, TA) and per link of
+# Wilson-clover force, flop per link (force kernel: three clover planes of 14 products, the 18
+# with an insertion without its real diagonal, hopping outer products, U B' and C' U^+, TA) and per link of
 # the clover-insertion pass (6 colour matrices per site from X, Y); minimum bytes per
 # link in reals: force = U (two rows) + G + a quarter of the site's X, Y (24 complex) and
 # K (six anti-Hermitian matrices, 9 reals each).
-WILSON_FLOP = {"wilson_force": 11262, "wilson_clover": 500}
+WILSON_FLOP = {"wilson_force": 9010, "wilson_clover": 500}
 WILSON_REALS = {"wilson_force": 12 + 18 + (48 + 54) / 4, "wilson_clover": (48 + 54) / 4}
 KAPPA, CSW = 0.1242, 1.37
 
