@@ -161,9 +161,11 @@ int md_leapfrog(const int32_t L[4], double u0, double beta, int prec, void* U, v
  * per lattice. ws: at least sym_batch_workspace_bytes(n, L, prec) bytes (0 if invalid).
  * The schedule (number of persistent workgroups, or one workgroup per tile; tile order;
  * links per workgroup; occupancy cap) is the one sym_batch_autotune chose for these
- * shapes and precision in this process, else one workgroup of 128 links per tile in an
- * XCD-contiguous order without an occupancy cap. Every schedule gives the same
- * forces; the actions agree to rounding (the partial sums are grouped by workgroup).
+ * shapes and precision in this process, else one workgroup per tile in an XCD-contiguous
+ * order: of 128 links without an occupancy cap, or in FP32, where a launch is few rounds
+ * of the waves that are resident at a time, of 256 links with a cap of two workgroups per
+ * CU. Every schedule gives the same forces; the actions agree to rounding (the partial
+ * sums are grouped by workgroup).
  */
 size_t sym_batch_workspace_bytes(int n, const int32_t* L, int prec);
 int sym_force_batch(int n, const int32_t* L, double u0, double beta, int prec, const void* const* U, void* const* F,

@@ -398,18 +398,41 @@ std::vector<int> tune_key(int n, const int32_t* L, int prec) {
   return k;
 }
 
-Schedule default_schedule(int) {
-  // one workgroup of 128 links per tile, XCD-contiguous, as many as the registers allow
-  // (two waves per SIMD in FP32, one in FP64). Against workgroups of 256 links under an LDS
-  // cap, with the chunks of each lattice in order: 60 lattices from {8^4, 12^4, 16^3 x 32}
-  // FP32 4.32 -> 4.27 ms, FP64 8.91 -> 8.37 ms; 3 of 32^3 x 16 2.43 -> 2.22 and 4.94 -> 4.34 ms;
-  // 64 of 8^4 0.344 -> 0.333 and 0.663 -> 0.637 ms.
-  return Schedule{0, 1, 128, 0};
+// The schedule of a launch over g[0..n) without a tuned one: one workgroup per tile in
+// XCD-contiguous order. FP64: 128 links, as many workgroups as the registers allow (one wave
+// per SIMD): faster than 256 at every size measured, or equal (60 lattices from {8^4, 12^4,
+// 16^3 x 32} 8.91 -> 8.37 ms; 3 of 32^3 x 16 4.94 -> 4.34; 64 of 8^4 0.621 -> 0.608).
+// FP32 (us of both passes, 256 links under the LDS cap against 128 without): with S = 2,048
+// waves resident (two per SIMD), workgroups of four waves spread them evenly over a CU's
+// SIMDs, workgroups of two need not, which costs most while the launch is few rounds of S
+// waves; many rounds level out, and then the finer tiles leave less idle.
+//   up to S/2 waves  256 links: 4 of 8^4 39.7 and 41.1, one 10^4 39.0 and 40.3;
+//   up to S          128 links (fewer SIMDs get a second wave): 13 of 6^4 47.4 and 45.2,
+//                    one 12^4 45.3 and 42.5;
+//   up to 6 S        256 links: 8 of 8^3 x 16 (2 S) 78.7 and 87.1, 32 of 8^4 (4 S) 152 and 160,
+//                    24 of 8^3 x 16 (6 S) 225 and 230; only up to 3 S where most tiles are
+//                    walked (planes of whole tiles, see walk_chunk): 6 of 16^2 x 8^2 (3 S) 120
+//                    and 127, but 2 of 16^4 (4 S) 161 and 157;
+//   above            128 links: 48 of 8^3 x 16 (12 S) 478 and 474, 2 of 16^3 x 32 (8 S) 334 and 321.
+Schedule default_schedule(int prec, const Geom* g, int n) {
+  const Schedule fine{0, 1, 128, 0}, even{0, 1, 256, -1};
+  if (prec == SYM_F64) return fine;
+  constexpr long long S = 2 * 4 * sym::kCUs;
+  long long waves = 0, walked = 0;
+  for (int i = 0; i < n; ++i) {
+    const long long w = sym::link_tiles(g[i], 64);
+    waves += w;
+    if (g[i].Lxh * g[i].L[1] % fine.links == 0) walked += w;
+  }
+  const long long most = (2 * walked > waves ? 3 : 6) * S;
+  return waves <= S / 2 || (waves >= S && waves <= most) ? even : fine;
 }
 
+// tuned: the schedule of every launch, or null for the default of each.
 template <typename T>
 hipError_t force_batch_run(int n, const BatchPlan& plan, const Coeffs& c, const void* const* U, void* const* F,
-                           double* S_dev, void* ws, const Schedule& sch, hipStream_t s) {
+                           double* S_dev, void* ws, const Schedule* tuned, hipStream_t s) {
+  constexpr int prec = sizeof(T) == 8 ? SYM_F64 : SYM_F32;
   char* base = static_cast<char*>(ws);
   double* parts = reinterpret_cast<double*>(base);
   hipError_t e = hipSuccess;
@@ -417,6 +440,7 @@ hipError_t force_batch_run(int n, const BatchPlan& plan, const Coeffs& c, const 
     sym::BatchTable b;
     memset(&b, 0, sizeof b);
     b.n = (n - c0) < sym::kMaxBatch ? (n - c0) : sym::kMaxBatch;
+    const Schedule sch = tuned ? *tuned : default_schedule(prec, &plan.g[c0], b.n);
     b.order = sch.order;
     int tiles = 0, site_tiles = 0;
     for (int k = 0; k < b.n; ++k) {
@@ -562,15 +586,19 @@ int sym_force_batch(int n, const int32_t* L, double u0, double beta, int prec, c
     return rc;
   if (ws_bytes < plan.total) return SYM_EWORKSPACE;
   if ((rc = check_batch_disjoint(n, plan, prec, U, F, S_dev, ws))) return rc;
-  Schedule sch = default_schedule(prec);
+  Schedule sch;
+  const Schedule* tuned = nullptr;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune.find(tune_key(n, L, prec));
-    if (it != g_tune.end()) sch = it->second;
+    if (it != g_tune.end()) {
+      sch = it->second;
+      tuned = &sch;
+    }
   }
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-  const hipError_t e = prec == SYM_F64 ? force_batch_run<double>(n, plan, c, U, F, S_dev, ws, sch, s)
-                                       : force_batch_run<float>(n, plan, c, U, F, S_dev, ws, sch, s);
+  const hipError_t e = prec == SYM_F64 ? force_batch_run<double>(n, plan, c, U, F, S_dev, ws, tuned, s)
+                                       : force_batch_run<float>(n, plan, c, U, F, S_dev, ws, tuned, s);
   return hip_status(e);
 }
 
@@ -592,7 +620,7 @@ int sym_batch_autotune(int n, const int32_t* L, double u0, double beta, int prec
     if (a) (void)hipEventDestroy(a);
     return SYM_EHIP;
   }
-  Schedule best = default_schedule(prec);
+  Schedule best{};
   float best_ms = -1.0f;
   int nlog = 0;
   // links per workgroup x occupancy cap (LDS KiB per workgroup: none, the default, one
@@ -609,8 +637,8 @@ int sym_batch_autotune(int n, const int32_t* L, double u0, double beta, int prec
         for (int order = 0; order < 2 && e == hipSuccess; ++order) {
           const Schedule sch{grid, order, linkss[li], lds};
           auto run = [&] {
-            return prec == SYM_F64 ? force_batch_run<double>(n, plan, c, U, F, nullptr, ws, sch, s)
-                                   : force_batch_run<float>(n, plan, c, U, F, nullptr, ws, sch, s);
+            return prec == SYM_F64 ? force_batch_run<double>(n, plan, c, U, F, nullptr, ws, &sch, s)
+                                   : force_batch_run<float>(n, plan, c, U, F, nullptr, ws, &sch, s);
           };
           if ((e = run()) != hipSuccess) break;  // warm-up
           if ((e = hipEventRecord(a, s)) != hipSuccess) break;
