@@ -12,19 +12,32 @@ namespace {
 
 // Tiles of the passes that read intermediate fields at neighbouring links: the walk of the
 // force pass (force_tile) with the parity fastest, so that the two parities of a chunk, which
-// read each other's fields, run side by side. These passes are bound by field data from
-// beyond the L2. FP32 at 32^3 x 64, against direction fastest in t-fastest slabs: FK2 2.65 ->
-// 2.56, FK3 1.44 -> 1.38, BK2 2.89 -> 2.88 ms (FK1, which reads links only, was slower, 1.06 ->
-// 1.12 ms, and keeps link_tile, as does BK3); 24^3 x 48, where the walk does not apply and only
-// the parity moves: 0.835 -> 0.810, 0.456 -> 0.451, 0.921 -> 0.908 ms, and GK, which in FP32
-// keeps this order there, 2.13 -> 2.11 ms.
-// FP64 at 32^4: FK2 2.23 -> 2.19, FK3 1.34 -> 1.26, BK2 2.62 -> 2.60 ms.
+// read each other's fields, run side by side. On large lattices these passes are bound by field
+// data from beyond the L2.
 __device__ __forceinline__ LinkTile fat_tile(const Geom& g, int linear, int ntiles) {
   LinkTile lt = force_tile(g, linear, ntiles, kBlock);
   const int q = lt.p * 4 + lt.mu;
   lt.p = q & 1;
   lt.mu = q >> 1;
   return lt;
+}
+
+// ... of FK2, FK3 and (BK2) the reverse pass, above 2^17 sites. Against direction fastest in
+// t-fastest slabs (link_tile), us: FP32 32^4 FK2 1293 -> 1213, BK2 1423 -> 1378; 20^3 x 40, where the
+// walk does not apply and only the parity moves, FK3 231 -> 226, FK2 394 -> 386; FP64 32^4 FK3
+// 1327 -> 1260, FK2 2214 -> 2182, 24^3 x 48 847 -> 822 and 1471 -> 1432. Below, much of the fields is
+// in the Infinity Cache and link_tile is as fast or faster: 32 x 16^3 FP32 FK3 91 and 93, BK2
+// 160 and 163, FP64 FK2 248 and 253, FK3 162 and 166, BK2 291 and 300. BK2 in FP64 gains by the
+// walk (16 x 32 x 16 x 64 1276 -> 1220, 32^4 2606 -> 2578) but not by the parity alone (16^2 x 32^2
+// 567 and 582, 20^3 x 40 801 and 805). FK1, which reads links only, was slower in this order
+// throughout (1.06 and 1.12 ms in FP32 at 32^3 x 64), BK3 no faster.
+constexpr int kFatTileVh = 1 << 16;
+
+template <typename T, bool BK2>
+__device__ __forceinline__ LinkTile field_tile(const Geom& g, int linear, int ntiles) {
+  const bool walk_only = BK2 && sizeof(T) == 8;
+  if (g.Vh <= kFatTileVh || (walk_only && !planes_are_chunks(g, kBlock))) return link_tile(g, linear, ntiles);
+  return fat_tile(g, linear, ntiles);
 }
 
 // The link of a thread of the gradient gather GK, which reads the most fields: a workgroup of
@@ -35,7 +48,8 @@ __device__ __forceinline__ LinkTile fat_tile(const Geom& g, int linear, int ntil
 // 32 x 24^2 x 32 3.49 -> 3.15, 32 x 16 x 32 x 16 1.50 -> 1.40, 32 x 16^2 x 48 2.37 -> 2.34 ms. FP64
 // planes below a workgroup (16^3 x 32) take 0.685 ms in fours, 0.665 in twos, which is where
 // they were. Planes that are not whole runs of 64 gain nothing from eight planes of 32 links
-// (FP64 24^4 1.94 ms either way) and keep the orders named. The other passes lose by the blocks
+// (FP64 24^4 1.94 ms either way) and keep fat_tile (FP32: 24^3 x 48 2.13 -> 2.11 ms) and link_tile
+// (FP64). The other passes lose by the blocks
 // on some lattices what they gain on others (FP64 FK2 and BK2 at 32^4 2.18 -> 2.06 and 2.59 ->
 // 2.48, at 32 x 16^2 x 48 0.79 -> 0.83 and 0.93 -> 1.03 ms).
 template <typename T>
@@ -81,7 +95,7 @@ __global__ __launch_bounds__(kBlock) void fat_fk1_kernel(Geom g, const T* __rest
 template <typename T>
 __global__ __launch_bounds__(kBlock) void fat_fk2_kernel(Geom g, const T* __restrict__ U, Fields<T> w, FatCoeffs cf,
                                                           int ntiles) {
-  const LinkTile lt = fat_tile(g, blockIdx.x, ntiles);
+  const LinkTile lt = field_tile<T, false>(g, blockIdx.x, ntiles);
   const int cb = lt.chunk * kBlock + threadIdx.x;
   if (cb >= g.Vh) return;
   Ctx<T> c;
@@ -120,7 +134,7 @@ template <typename T>
 __global__ __launch_bounds__(kBlock) void fat_fk3_kernel(Geom g, const T* __restrict__ U, Fields<T> w,
                                                           T* __restrict__ V, T* __restrict__ W, FatCoeffs cf,
                                                           int ntiles) {
-  const LinkTile lt = fat_tile(g, blockIdx.x, ntiles);
+  const LinkTile lt = field_tile<T, false>(g, blockIdx.x, ntiles);
   const int cb = lt.chunk * kBlock + threadIdx.x;
   if (cb >= g.Vh) return;
   Ctx<T> c;
@@ -150,7 +164,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T
 template <typename T>
 __global__ __launch_bounds__(kBlock) void fat_bk2_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
                                                           Fields<T> w, FatCoeffs cf, int ntiles) {
-  const LinkTile lt = fat_tile(g, blockIdx.x, ntiles);
+  const LinkTile lt = field_tile<T, true>(g, blockIdx.x, ntiles);
   const int cb = lt.chunk * kBlock + threadIdx.x;
   if (cb >= g.Vh) return;
   Ctx<T> c;
