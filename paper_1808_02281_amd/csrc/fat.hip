@@ -251,8 +251,11 @@ __global__ __launch_bounds__(kBlock) void fat_gk_kernel(Geom g, const T* __restr
 
 // ------------------------------------------------------------ small lattices
 // With one wave per 64 links small lattices leave most SIMDs empty and wait for one wave's
-// serial products. Here a workgroup of four waves shares 64 links (one per lane of every
-// wave), with partial sums in LDS. That pays up to two workgroups per CU (kFatSmallTiles).
+// serial products. Here a workgroup of three or four waves shares 64 links (one per lane of
+// every wave), with partial sums in LDS, so that the results are those of the whole-link form
+// to rounding: each wave's sum starts from zero and the sums are added. That pays up to 512
+// workgroups (kFatSmallTiles), which in FP64 run in two rounds: FK2, BK2 and GK take more than
+// 256 registers and so one workgroup per CU.
 // Path force, before -> now: FP32 4^4 81 -> 42 us, 8^4 104 -> 47, 8^3 x 16 (512 workgroups) 107 -> 65;
 // FP64 4^4 90 -> 46 us, 8^4 124 -> 54, 8^3 x 16 136 -> 98. With 1024 workgroups (8^2 x 16^2) it would
 // be 117 -> 117 us in FP32 and 172 -> 194 us in FP64.
@@ -305,7 +308,9 @@ __global__ __launch_bounds__(192) void fat_bk3_small_kernel(Geom g, const T* __r
 }
 
 // FK2 and BK2, first half: wave J-1 forms the transports along ax[J], which serve the two
-// outputs other than J, into LDS slots 3 (J-1) + output.
+// outputs k other than J-1, into LDS.
+constexpr int kTransports = 6;
+constexpr int transport_slot(int J, int k) { return 2 * (J - 1) + (k > J - 1 ? k - 1 : k); }
 template <int J, bool BACK, typename T>
 __device__ __forceinline__ void small_two_out(const SmallLink<T>& s, const T* F, const LdsMats<T>& m) {
   su3<T> acc[3];
@@ -314,7 +319,7 @@ __device__ __forceinline__ void small_two_out(const SmallLink<T>& s, const T* F,
   fat::two_out_one<J, BACK>(acc, s.c, F);
 #pragma unroll
   for (int k = 0; k < 3; ++k)
-    if (k != J - 1) m.put(3 * (J - 1) + k, acc[k]);
+    if (k != J - 1) m.put(transport_slot(J, k), acc[k]);
 }
 template <bool BACK, typename T>
 __device__ __forceinline__ void small_transports(const SmallLink<T>& s, const T* F, const LdsMats<T>& m) {
@@ -332,8 +337,8 @@ __device__ __forceinline__ void small_transports(const SmallLink<T>& s, const T*
 template <typename T>
 __device__ __forceinline__ void small_sum(su3<T>& acc, int k, const LdsMats<T>& m) {
 #pragma unroll
-  for (int j = 0; j < 3; ++j)
-    if (j != k) add(acc, m.get(3 * j + k));
+  for (int J = 1; J <= 3; ++J)
+    if (J - 1 != k) add(acc, m.get(transport_slot(J, k)));
 }
 
 template <int K, typename T>
@@ -347,7 +352,7 @@ __device__ __forceinline__ void small_m(const SmallLink<T>& s, const Fields<T>& 
 
 template <typename T>
 __global__ __launch_bounds__(192) void fat_fk2_small_kernel(Geom g, const T* __restrict__ U, Fields<T> w, FatCoeffs cf) {
-  __shared__ T lds[9 * 18 * 64];
+  __shared__ T lds[kTransports * 18 * 64];
   const SmallLink<T> s = small_link(g, U);
   const LdsMats<T> m{lds, (int)(threadIdx.x & 63)};
   small_transports<false>(s, static_cast<const T*>(w.inner), m);
@@ -372,7 +377,7 @@ __device__ __forceinline__ void small_gt(const SmallLink<T>& s, const T* GV, con
 template <typename T>
 __global__ __launch_bounds__(256) void fat_bk2_small_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ GV,
                                                             Fields<T> w, FatCoeffs cf) {
-  __shared__ T lds[9 * 18 * 64];
+  __shared__ T lds[kTransports * 18 * 64];
   const SmallLink<T> s = small_link(g, U);
   const LdsMats<T> m{lds, (int)(threadIdx.x & 63)};
   small_transports<true>(s, static_cast<const T*>(w.gmid), m);
