@@ -12,7 +12,8 @@
 // flight on an XCD within its 4 MiB of L2 (1.5 GB fetched), in the t-fastest slab order of the
 // other passes, and small lattices get four times the waves with a quarter of the serial work
 // each. The axes are wave-uniform values rather than template arguments, so the four waves
-// share one code. The bound now is the vector load path (TD busy 0.94 in FP64, VALU 0.44).
+// share one code. The bound now is the vector load path (TD busy 0.94 in FP64, VALU 0.44): 140
+// matrices are loaded per site (FP32 160), half of them L1 hits and most of the rest L2 hits.
 //
 // FP32 multiplies every loop out from its base site link by link (loops that start with the
 // same two links share that product): the double sums carry the float rounding of every

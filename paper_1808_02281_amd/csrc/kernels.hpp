@@ -61,7 +61,8 @@ constexpr int factored_links() {
 //     in FP32 and 3 in FP64 on 1024 SIMDs. FP32 12^4 (5,832 waves) 20 -> 12 us, 16^4
 //     (18,432) 21 -> 29 us; FP64 8^3 x 16 (2,304) 21 -> 11 us, 12^4 22 -> 20 us, 16^4 39 -> 53 us;
 //   force, eight waves per 64 links: while every workgroup has a CU of its own. 8^4 (256
-//     workgroups) FP32 22 -> 15 us, FP64 25 -> 20 us; 8^3 x 16 23 -> 26 and 27 -> 35 us.
+//     workgroups) FP32 22 -> 15 us, FP64 25 -> 19 us; 8^3 x 10 (320) 22.8 -> 24.0 and 28.2 -> 30.8 us,
+//     8^3 x 16 (512) 24.0 -> 25.7 and 29.4 -> 32.9 us.
 constexpr int kCUs = 256;
 constexpr int kStapleRoles = 18;  // steps of a site's staples
 template <typename T>

@@ -499,8 +499,11 @@ __device__ __forceinline__ void store_wilson(const WCtx<T>& c, T* out, int cb, c
 // FP32: two waves per SIMD (199 VGPRs); three would spill: 1.75 against 1.50 ms at
 // 32^3 x 64. FP64: one wave (256 VGPRs and 162 AGPRs). With one sum over s per plane,
 // projected spinors and the insertions' zero parts left out, FP32 1.63 -> 1.46 ms at 32^3 x 64,
-// FP64 1.05 -> 0.96 ms at 24^3 x 48. (abd as two rows with the third rebuilt would save another
-// 2%, at an error against 64 bits that is no longer below that of the separate plaquettes.)
+// FP64 1.05 -> 0.96 ms at 24^3 x 48. Where a lattice has 2,049 to 3,072 waves, which take two rounds
+// at two waves per SIMD and took one at three, FP32 gains nothing: 14 x 12 x 14^2 43.2 -> 43.0 us a call,
+// 16 x 12 x 14^2 41.8 -> 42.1, 14^4 43.4 -> 43.5, 16^3 x 12 45.1 -> 43.6. (abd as two rows with the third
+// rebuilt would save another 2%, at an error against 64 bits that is no longer below that of
+// the separate plaquettes.)
 template <typename T>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : 1))) void
 wilson_force_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ X, const T* __restrict__ Y,
@@ -528,8 +531,10 @@ wilson_force_kernel(Geom g, const T* __restrict__ U, const T* __restrict__ X, co
 // Small lattices: four waves share 64 links (one per lane of every wave), waves 0..2 the
 // clover leaves of a plane each, wave 3 the hopping terms, joined in LDS. With a wave per 64
 // links the clover term is a serial stream of 5,500 instructions whatever the lattice. The
-// same operations in the same order: bitwise the same force. It pays up to two workgroups
-// per CU: 4^4 FP32 20 -> 9 us, FP64 21 -> 11 us; 8^3 x 16 (512 workgroups) 22 -> 13 and 26 -> 21 us.
+// same operations in the same order: bitwise the same force. It pays up to two workgroups per CU:
+// kernel 4^4 FP32 20 -> 9 us, FP64 21 -> 11 us; 8^3 x 16 (512 workgroups) 22 -> 13 and 26 -> 21 us.
+// Above, FP64 loses (8^3 x 18, 576: 24.3 -> 27.7 us; 1,024: 27.4 -> 37.9) and FP32 gains little (576 to
+// 768: 20 -> 17.5 us) or loses (1,024: 21.3 either way; 12^4, 1,296: 25.9 -> 27.3).
 template <typename T>
 __global__ __launch_bounds__(256) void wilson_force_small_kernel(Geom g, const T* __restrict__ U,
                                                                  const T* __restrict__ X, const T* __restrict__ Y,
